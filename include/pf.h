@@ -113,7 +113,8 @@ typedef struct {
     double inner_tol;      /* PF_MIXED: relative residual target of each inner solve */
     int32_t max_refine;    /* PF_MIXED: maximum refinement steps                     */
     int32_t check_every;   /* iterations per device-side chunk between host checks;
-                              0 = library default                                     */
+                              0 = library default (on chip where the grid fits: no
+                              host check until the run ends)                          */
     int32_t stop_rule;     /* pf_stop_rule                                            */
 } pf_lin_opts;
 
@@ -267,6 +268,8 @@ pf_status pf_nonlinear_solve_batch(int32_t n, pf_grid *const *g, const pf_pf_par
  * stencil kernel (the previous iteration's x, r update fused with the p
  * update and v = A p^: the kernel that moves the most bytes per iteration);
  * every Jacobi-scaled pf_spmv / pf_spmv_f32 call is timed the same way.
+ * Solves that otherwise run on chip (one launch per Krylov run) use the
+ * two-kernel iteration while timing is enabled.
  * enable = 1 clears the accumulators and starts; 0 stops.  Process-wide. */
 pf_status pf_timing_enable(int32_t enable, int32_t sample);
 
@@ -412,8 +415,9 @@ const char *pf_last_error(void);
 /* Launch-shape override for tests and tuning: points per workgroup strip,
  * z-planes per workgroup, threads per workgroup, and planes of loads kept in
  * flight ahead of the plane being computed (pipeline 1 or 2).  0 =
- * autotuned/default for each.  Applies to grids created afterwards (and
- * turns the autotuner off while any override is set).  Returns PF_ERR_ARG
+ * autotuned/default for each.  Applies to grids created afterwards (their
+ * solves use the two-kernel iteration, not the on-chip one) and
+ * turns the autotuner off while any override is set.  Returns PF_ERR_ARG
  * for unsupported shapes. */
 pf_status pf_set_launch(int32_t strip, int32_t zdepth, int32_t threads, int32_t pipeline);
 

@@ -8,11 +8,11 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SRC = os.path.join(HERE, "csrc", "pf_host.hip")
+SRCS = [os.path.join(HERE, "csrc", f) for f in ("pf_host.hip", "pf_chip.hip")]
 LIB = os.path.join(HERE, "libpf.so")
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed FP32 instructions stay off (see the design notes on FP32 correctness)
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-result",
@@ -24,14 +24,30 @@ def hipcc():
 
 
 def build(verbose: bool = False) -> str:
+    """Compile every source (side by side) and link libpf.so."""
+    objs, jobs = [], []
+    for src in SRCS:
+        obj = src + ".o"
+        cmd = [hipcc(), *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-c", "-o", obj, src]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        objs.append(obj)
+        jobs.append(subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))
+    failed = False
+    for src, job in zip(SRCS, jobs):
+        out = job.communicate()[0]
+        if job.returncode != 0:
+            sys.stderr.write(out)
+            failed = True
+    if failed:
+        raise RuntimeError("hipcc failed building libpf.so")
     tmp = LIB + ".tmp"
-    cmd = [hipcc(), *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-o", tmp, SRC]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
+    res = subprocess.run([hipcc(), "--offload-arch=gfx950", "-shared", "-o", tmp, *objs], capture_output=True, text=True)
+    for obj in objs:
+        os.remove(obj)
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
-        raise RuntimeError("hipcc failed building libpf.so")
+        raise RuntimeError("hipcc failed linking libpf.so")
     os.replace(tmp, LIB)
     return LIB
 

@@ -1,13 +1,15 @@
 // pf_host.hip -- host side of the C-ABI in include/pf.h.
 //
 // Grid handles own device copies of the fields and the solver workspace.
-// Linear solves run the Jacobi-BiCGSTAB of Sec. 4, Table 3 with three fused
-// kernels per iteration (pf_kernels.h); the scalar recurrences stay on the
-// device and the host reads one small status block per chunk of iterations.
-// Each chunk is a captured hipGraph, so a chunk costs one launch.  The
+// Linear solves run the Jacobi-BiCGSTAB of Sec. 4, Table 3: a grid that fits
+// the chip's registers and LDS in one launch per Krylov run (pf_chip.hip),
+// others with two fused kernels per iteration (pf_kernels.h).  The scalar
+// recurrences stay on the device; of the two-kernel iteration the host reads
+// one small status block per chunk of iterations, a captured hipGraph.  The
 // nonlinear loop of Tables 2 and 4 runs entirely on the device apart from one
 // status read per outer iteration (the max-norm test of Table 2 step 5).
 #include "pf_kernels.h"
+#include "pf_chip.h"
 #include <hip/hip_ext.h>
 #include "pf_iface.h"
 #include "pf_sites.h"
@@ -207,6 +209,16 @@ struct pf_grid {
     bool last_timed_first = false;   // the first chunk of the last batch ran timed
     int last_run[4] = {0, 0, 0, 0};    // iterations of the last Krylov run per (precision, system)
 
+    // on-chip Krylov runs (pf_chip.h)
+    bool pinned_shape = false;         // created under a launch override: the two-kernel iteration only
+    bool chip_off = false;             // an on-chip run gave up waiting: the two-kernel iteration from then on
+    bool tuned = false, tuned32 = false;
+    std::map<std::tuple<int, int, int>, pfk::ChipGeom> chip_geoms;   // per (PF1, planes per tile, tile limit)
+    void *chip_table = nullptr;        // the system of a single run
+    char *chip_xch = nullptr;          // exchange buffers
+    size_t chip_xch_bytes = 0;
+    unsigned chip_tag = 0;             // next unused exchange tag (0: buffers not cleared yet)
+
     // nonlinear state
     double *phi0 = nullptr, *phi = nullptr, *psi = nullptr, *rhs1 = nullptr, *sig = nullptr,
            *rhs2 = nullptr, *src = nullptr;
@@ -252,9 +264,6 @@ pf_status sync(pf_grid *g)
 }
 
 template <typename T>
-pf_status tune(pf_grid *g);
-
-template <typename T>
 pf_status ensure_work(pf_grid *g)
 {
     if constexpr (sizeof(T) == 8) {
@@ -265,7 +274,6 @@ pf_status ensure_work(pf_grid *g)
             PFCHK(dalloc(g, p, g->N));
         PFCHK(dalloc(g, &w.rt, g->N));
         g->have64 = true;
-        PFCHK(tune<double>(g));
     } else {
         if (g->have32) return PF_OK;
         PFCHK(ensure_work<double>(g));
@@ -278,7 +286,6 @@ pf_status ensure_work(pf_grid *g)
                            g->N, (const double *)g->eps64, g->eps32);
         HIPCHK(hipGetLastError());
         g->have32 = true;
-        PFCHK(tune<float>(g));
     }
     return PF_OK;
 }
@@ -764,7 +771,9 @@ std::vector<ZCfg> tune_candidates(const pf_grid *g)
 template <typename T>
 pf_status tune(pf_grid *g)
 {
-    if (!tuning_enabled()) return PF_OK;
+    bool &done = sizeof(T) == 8 ? g->tuned : g->tuned32;
+    if (done || !tuning_enabled()) return PF_OK;
+    done = true;
     const auto key = std::make_tuple(g->nx, g->ny, g->nz, (int)sizeof(T));
     auto found = g_tuned.find(key);
     if (found != g_tuned.end()) {
@@ -967,11 +976,9 @@ struct StartRec {
 };
 std::vector<StartRec> *g_defer_start = nullptr;   // set while a batch decides its next runs
 
-template <typename T>
-pf_status krylov_start(pf_grid *g, Work<T> &w, double rr, double tol2, int iter, int maxit, bool zero_x = false)
+Scalars krylov_init(double rr, double tol2, int iter, int maxit)
 {
-    Scalars &h = *g->hsc;
-    h = Scalars{};
+    Scalars h{};
     h.rho[0] = rr;            // shadow = r, so rho_0 = ||r||^2
     h.alpha[1] = 1.0;
     h.omega[1] = 1.0;
@@ -984,6 +991,14 @@ pf_status krylov_start(pf_grid *g, Work<T> &w, double rr, double tol2, int iter,
     h.stop = pfk::ST_RUN;
     h.stop_a = pfk::ST_RUN;
     h.fresh = 1;
+    return h;
+}
+
+template <typename T>
+pf_status krylov_start(pf_grid *g, Work<T> &w, double rr, double tol2, int iter, int maxit, bool zero_x = false)
+{
+    Scalars &h = *g->hsc;
+    h = krylov_init(rr, tol2, iter, maxit);
     if (g_defer_start) {
         g_defer_start->push_back(StartRec{g, (int)sizeof(T), w.p[0], w.v[0], w.t, zero_x ? (void *)w.x : nullptr, h});
         return PF_OK;
@@ -1078,8 +1093,272 @@ struct LinSolve {
     int iter = 0, restarts = 0, refinements = 0;
     bool started = false, done = false, fallback = false;
     bool class_probe = false;   // the shift-per-class test ran in the set-up
+    bool chip = false;          // the coming Krylov run is an on-chip one
+    double run_tol2 = 0;        // its tolerance
     pf_status result = PF_OK;
 };
+
+// ------------------------------------------------------------ on-chip runs
+
+template <typename T>
+Work<T> &work_of(pf_grid *g)
+{
+    if constexpr (sizeof(T) == 8) return g->w64;
+    else return g->w32;
+}
+
+int chip_form(const LinSolve &L)
+{
+    if (L.op.psi) return pfk::CHF_CEPS;
+    if (!L.op.sigma) return pfk::CHF_NONE;
+    return L.op.sig_class ? pfk::CHF_CLASS : pfk::CHF_NODE;
+}
+
+// Planes per tile: the instances with 16 keep two palette classes per node
+// and have no registers left for a shift of its own.
+int chip_kzmax(const LinSolve &L)
+{
+    if (L.op.psi) return 16;
+    return (L.g->npal > 2 || chip_form(L) == pfk::CHF_NODE) ? 8 : 16;
+}
+
+// Iterations of one launch (a run that reaches them returns to the true
+// residual and starts again).
+constexpr int CHIP_MAX_RUN = 1 << 16;
+
+const pfk::ChipGeom &chip_geom(pf_grid *g, bool psi, int kzmax, int gcap)
+{
+    const auto key = std::make_tuple(psi ? 1 : 0, kzmax, gcap);
+    auto it = g->chip_geoms.find(key);
+    if (it == g->chip_geoms.end()) {
+        const pfk::ChipGeom ge = pfk::chip_partition(g->nx, g->ny, g->nz, psi ? g->bcpsi_mask : g->bcphi_mask, gcap, kzmax);
+        it = g->chip_geoms.emplace(key, ge).first;
+        if (ge.KZ > 0 && getenv("PF_LOG"))
+            fprintf(stderr, "[pf] on-chip runs of %dx%dx%d: %d x %d x %d tiles of up to %d planes\n", g->nx, g->ny, g->nz,
+                    ge.c[0], ge.c[1], ge.c[2], ge.KZ);
+    }
+    return it->second;
+}
+
+// Krylov runs of this solve go on chip where the unknowns fit it.  Not where
+// the caller asks for something of the two-kernel iteration itself: launch
+// shapes (pf_set_launch, PF_BATCH_POLICY), kernel timing, a status read
+// every check_every iterations; nor for fields without a palette.  PF_CHIP=0
+// turns it off (for comparisons).
+template <typename T>
+bool chip_fits(const LinSolve &L)
+{
+    pf_grid *g = L.g;
+    if (g->pinned_shape || g->chip_off || g_timing.enabled || L.o->check_every > 0) return false;
+    if (g_nt_override || g_ppt_override || g_kz_override || g_depth_override) return false;
+    if (!L.op.psi && !use_palette(g)) return false;
+    const char *e = getenv("PF_CHIP");
+    if (e && e[0] == '0') return false;
+    if (getenv("PF_BATCH_POLICY")) return false;
+    return chip_geom(g, L.op.psi, chip_kzmax(L), pfk::CH_GMAX).KZ > 0;
+}
+
+// Start of the next Krylov run: nothing to do yet for an on-chip run.
+template <typename T>
+pf_status ls_start(LinSolve &L, double tol2, bool zero_x)
+{
+    L.run_tol2 = tol2;
+    L.chip = chip_fits<T>(L);
+    if (!L.chip) return krylov_start<T>(L.g, work_of<T>(L.g), L.rr, tol2, L.iter, L.o->max_iter, zero_x);
+    *L.g->hsc = krylov_init(L.rr, tol2, L.iter, std::min(L.o->max_iter, L.iter + CHIP_MAX_RUN));
+    return PF_OK;
+}
+
+// Table entry of a run of L in the partition ge by the kernel instance of kz
+// planes; the exchange buffers grow to it.
+template <typename T>
+pf_status chip_system(LinSolve &L, const pfk::ChipGeom &ge, int kz, pfk::ChipSys<T> &S)
+{
+    pf_grid *g = L.g;
+    Work<T> &w = work_of<T>(g);
+    const size_t nsum = (size_t)2 * pfk::CH_NQ * ge.G * 16;
+    const size_t nface = ((size_t)2 * ge.G * ge.fstride * 2 * sizeof(T) + 255) & ~(size_t)255;
+    const size_t need = nsum + nface + (kz > 8 ? (size_t)ge.G * kz * pfk::CH_NT * sizeof(T) : 0);
+    if (need > g->chip_xch_bytes) {
+        PFCHK(dalloc(g, &g->chip_xch, need));
+        g->chip_xch_bytes = need;
+        g->chip_tag = 0;
+    }
+    // tags of this run: never used before on these buffers, which are cleared
+    // when the count starts again (tag 0 is never used)
+    constexpr unsigned RUN_TAGS = 2 * CHIP_MAX_RUN + 8;
+    if (g->chip_tag == 0 || g->chip_tag > ~0u - RUN_TAGS) {
+        PFCHK(fill<uint8_t>(g, reinterpret_cast<uint8_t *>(g->chip_xch), 0, g->chip_xch_bytes));
+        PFCHK(sync(g));
+        g->chip_tag = 1;
+    }
+    S = pfk::ChipSys<T>{};
+    S.nx = g->nx; S.ny = g->ny; S.nz = g->nz; S.P = g->nx * g->ny;
+    S.ge = ge;
+    S.zero_x = sizeof(T) == 4 ? 1 : 0;   // FP32 runs solve for a correction
+    const pfk::ZArgs<T> a = zbase<T>(g, L.op);
+    S.ceps = a.ceps; S.cdiag = a.cdiag; S.cidiag = a.cidiag;
+    S.dirbit = a.dirbit;
+    S.flags = a.flags; S.epsi = a.epsi;
+    S.ftab = a.ftab; S.stab = a.stab; S.sig = a.sig;
+    S.s0 = w.s;
+    S.rt = w.rt;
+    S.x = w.x;
+    S.sc = g->sc;
+    S.init = *g->hsc;
+    S.sums = g->chip_xch;
+    S.face = g->chip_xch + nsum;
+    S.xtile = reinterpret_cast<T *>(g->chip_xch + nsum + nface);
+    S.tag0 = g->chip_tag;
+    g->chip_tag += RUN_TAGS;
+    return PF_OK;
+}
+
+// Tiles wait for each other, so an on-chip launch needs its tiles resident
+// together: one such launch at a time per device (held until it has ended).
+// Other work on the device only delays it.
+std::mutex g_chip_mu[64];
+
+template <typename T>
+pf_status krylov_run(pf_grid *g, const OpDesc &op, Work<T> &w, int m_fixed, int *status, bool adaptive);
+
+// The tiles of an on-chip run gave up waiting: the same run by the
+// two-kernel iteration, from the start vectors it left untouched.
+template <typename T>
+pf_status chip_gave_up(LinSolve &L, int m, int *status)
+{
+    pf_grid *g = L.g;
+    g->chip_off = true;
+    PFCHK(krylov_start<T>(g, work_of<T>(g), L.rr, L.run_tol2, L.iter, L.o->max_iter, sizeof(T) == 4));
+    return krylov_run<T>(g, L.op, work_of<T>(g), m, status, L.o->check_every == 0);
+}
+
+template <typename T>
+pf_status chip_run(LinSolve &L, int m, int *status)
+{
+    pf_grid *g = L.g;
+    const pfk::ChipGeom &ge = chip_geom(g, L.op.psi, chip_kzmax(L), pfk::CH_GMAX);
+    if (!g->chip_table) {
+        char *p = nullptr;
+        PFCHK(dalloc(g, &p, std::max(sizeof(pfk::ChipSys<double>), sizeof(pfk::ChipSys<float>))));
+        g->chip_table = p;
+    }
+    pfk::ChipSys<T> S;
+    PFCHK(chip_system<T>(L, ge, ge.KZ, S));
+    auto *table = static_cast<pfk::ChipSys<T> *>(g->chip_table);
+    {
+        std::lock_guard<std::mutex> lock(g_chip_mu[g->device & 63]);
+        HIPCHK(pfk::chip_start<T>(&S, table, 1, g->stream));
+        HIPCHK(pfk::chip_launch<T>(chip_form(L), ge.KZ, table, nullptr, 1, ge.G, g->stream));
+        PFCHK(read_scalars(g));
+    }
+    *status = g->hsc->stop;
+    if (*status == pfk::ST_RUN) return chip_gave_up<T>(L, m, status);
+    return PF_OK;
+}
+
+// Device table of a batch's on-chip runs, grown on demand (one batch runs at
+// a time per process).
+struct ChipBuf {
+    void *dev = nullptr, *host = nullptr;
+    size_t bytes = 0;
+    Scalars *hsc = nullptr;
+    int hcap = 0;
+} g_chipb;
+
+// Tile limit of a batch member: its share of the chip by unknowns, or the
+// fewest tiles that hold it where the whole batch does not fit at once (the
+// tiles of later members then start as those of earlier ones end).
+template <typename T>
+const pfk::ChipGeom &chip_batch_geom(const LinSolve &L, double total)
+{
+    const int kz = chip_kzmax(L);
+    int cap = std::max(1, (int)(pfk::CH_GMAX * ((double)L.g->N / total)));
+    for (;; cap = std::max(cap + 1, cap * 9 / 8)) {
+        const pfk::ChipGeom &ge = chip_geom(L.g, L.op.psi, kz, std::min(cap, pfk::CH_GMAX));
+        if (ge.KZ > 0 || cap >= pfk::CH_GMAX) return ge;
+    }
+}
+
+// On-chip runs of several systems in one launch per kernel form.  Tiles are
+// dispatched in order, so the earliest unfinished system always has all of
+// its tiles on the chip.
+template <typename T>
+pf_status chip_run_batch(std::vector<LinSolve *> &act, hipStream_t stream, int m, std::vector<int> &status)
+{
+    const int n = (int)act.size();
+    status.assign(n, pfk::ST_RUN);
+    std::vector<int> order(n);
+    for (int i = 0; i < n; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+        const int fa = chip_form(*act[a]), fb = chip_form(*act[b]);
+        return fa != fb ? fa < fb : act[a]->g->N > act[b]->g->N;
+    });
+    auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    const size_t szT = al(sizeof(pfk::ChipSys<T>) * n), szF = al(sizeof(int) * (2 * n + 1)), szP = al(sizeof(void *) * n);
+    const size_t up = szT + szF + szP, need = up + al(sizeof(Scalars) * n);
+    if (need > g_chipb.bytes) {
+        if (g_chipb.dev) (void)hipFree(g_chipb.dev);
+        if (g_chipb.host) (void)hipHostFree(g_chipb.host);
+        g_chipb.dev = g_chipb.host = nullptr;
+        g_chipb.bytes = 0;
+        if (hipMalloc(&g_chipb.dev, need) != hipSuccess) return fail(PF_ERR_ALLOC, "batch table allocation failed");
+        if (hipHostMalloc(&g_chipb.host, need, hipHostMallocDefault) != hipSuccess)
+            return fail(PF_ERR_ALLOC, "batch pinned allocation failed");
+        g_chipb.bytes = need;
+    }
+    char *hb = static_cast<char *>(g_chipb.host), *db = static_cast<char *>(g_chipb.dev);
+    auto *hsys = reinterpret_cast<pfk::ChipSys<T> *>(hb);
+    int *hfirst = reinterpret_cast<int *>(hb + szT);
+    auto **hscp = reinterpret_cast<const Scalars **>(hb + szT + szF);
+    auto *hgather = reinterpret_cast<Scalars *>(hb + up);
+    double total = 0;
+    for (const LinSolve *L : act) total += (double)L->g->N;
+    struct Launch { int form, kz, at, n, tiles, foff; };
+    std::vector<Launch> ls;
+    std::vector<const pfk::ChipGeom *> geo(n);
+    int foff = 0;
+    for (int i = 0; i < n; ++i) {
+        geo[i] = &chip_batch_geom<T>(*act[order[i]], total);
+        const int form = chip_form(*act[order[i]]);
+        if (ls.empty() || ls.back().form != form) {
+            if (!ls.empty()) ++foff;
+            ls.push_back(Launch{form, 0, i, 0, 0, foff});
+            hfirst[foff] = 0;
+        }
+        Launch &b = ls.back();
+        b.kz = std::max(b.kz, geo[i]->KZ);
+        b.n += 1;
+        b.tiles += geo[i]->G;
+        hfirst[++foff] = b.tiles;
+    }
+    for (const Launch &b : ls)
+        for (int i = b.at; i < b.at + b.n; ++i) {
+            PFCHK(chip_system<T>(*act[order[i]], *geo[i], b.kz, hsys[i]));
+            hscp[i] = act[order[i]]->g->sc;
+        }
+    {
+        std::lock_guard<std::mutex> lock(g_chip_mu[act[0]->g->device & 63]);
+        HIPCHK(hipMemcpyAsync(db, hb, up, hipMemcpyHostToDevice, stream));
+        HIPCHK(pfk::chip_start<T>(nullptr, reinterpret_cast<pfk::ChipSys<T> *>(db), n, stream));
+        for (const Launch &b : ls)
+            HIPCHK(pfk::chip_launch<T>(b.form, b.kz, reinterpret_cast<pfk::ChipSys<T> *>(db) + b.at,
+                                       reinterpret_cast<int *>(db + szT) + b.foff, b.n, b.tiles, stream));
+        hipLaunchKernelGGL(pfk::k_gather_scalars, dim3((n + 63) / 64), dim3(64), 0, stream,
+                           reinterpret_cast<const Scalars *const *>(db + szT + szF),
+                           reinterpret_cast<Scalars *>(db + up), n);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipMemcpyAsync(hgather, db + up, sizeof(Scalars) * n, hipMemcpyDeviceToHost, stream));
+        HIPCHK(hipStreamSynchronize(stream));
+    }
+    for (int i = 0; i < n; ++i) {
+        *act[order[i]]->g->hsc = hgather[i];
+        status[order[i]] = hgather[i].stop;
+    }
+    for (int i = 0; i < n; ++i)
+        if (status[i] == pfk::ST_RUN) PFCHK(chip_gave_up<T>(*act[i], m, &status[i]));
+    return PF_OK;
+}
 
 // True residual of the current x into red[0] (and the shadow / FP32 copies
 // the next Krylov run starts from).  Asynchronous.
@@ -1109,6 +1388,12 @@ pf_status ls_init_launch(LinSolve &L)
     PFCHK(ensure_work<double>(g));
     L.mixed = L.o->precision == PF_MIXED;
     if (L.mixed) PFCHK(ensure_work<float>(g));
+    // launch shapes of the two-kernel iteration, where a run will use it
+    // (tuning overwrites the Krylov vectors, not b or x)
+    if (L.mixed ? !chip_fits<float>(L) : !chip_fits<double>(L)) {
+        PFCHK(tune<double>(g));
+        if (L.mixed) PFCHK(tune<float>(g));
+    }
     if (L.op.sigma) {   // sigma >= 0 on free rows, read back with ||b_lift||
         PFCHK(fill<int>(g, &g->sc->neg_shift, 0, 1));
         hipLaunchKernelGGL(pfk::k_check_shift, dim3(pw_blocks(g->N)), dim3(NT), 0, g->stream, g->N, L.op.sigma,
@@ -1240,7 +1525,7 @@ pf_status ls_round_decide(LinSolve &L, bool *run)
         if (L.started) ++L.restarts;
         if (L.restarts > 1000) { L.result = PF_ERR_BREAKDOWN; L.done = true; return PF_OK; }
         L.started = true;
-        PFCHK(krylov_start<double>(g, g->w64, L.rr, L.tol2, L.iter, L.o->max_iter));
+        PFCHK(ls_start<double>(L, L.tol2, false));
     } else {
         if (L.refinements >= L.o->max_refine || L.iter >= L.o->max_iter) {
             L.result = PF_ERR_NOCONV;
@@ -1250,7 +1535,7 @@ pf_status ls_round_decide(LinSolve &L, bool *run)
         ++L.refinements;
         L.rr_start = L.rr;
         const double itol2 = L.o->inner_tol * L.o->inner_tol;
-        PFCHK(krylov_start<float>(g, g->w32, L.rr, std::max(itol2 * L.rr, L.tol2), L.iter, L.o->max_iter, true));
+        PFCHK(ls_start<float>(L, std::max(itol2 * L.rr, L.tol2), true));
     }
     *run = true;
     return PF_OK;
@@ -1325,7 +1610,8 @@ pf_status solve_internal(pf_grid *g, const OpDesc &op, const pf_lin_opts *o, pf_
         if (!run) break;
         int st = 0;
         const bool adaptive = o->check_every == 0;
-        if (L.mixed) PFCHK(krylov_run<float>(g, L.op, g->w32, m, &st, adaptive));
+        if (L.chip) PFCHK(L.mixed ? chip_run<float>(L, m, &st) : chip_run<double>(L, m, &st));
+        else if (L.mixed) PFCHK(krylov_run<float>(g, L.op, g->w32, m, &st, adaptive));
         else PFCHK(krylov_run<double>(g, L.op, g->w64, m, &st, adaptive));
         PFCHK(ls_after(L, st));
     }
@@ -2019,9 +2305,18 @@ pf_status solve_batch(std::vector<LinSolve> &Ls)
         if (!batched)
             for (LinSolve *L : act) PFCHK(sync(L->g));   // Krylov starts written
         // members that fell back to FP64 run apart from those still refining in FP32
-        std::vector<LinSolve *> a32, a64;
-        for (LinSolve *L : act) (L->mixed ? a32 : a64).push_back(L);
+        std::vector<LinSolve *> a32, a64, c32, c64;
+        for (LinSolve *L : act) (L->chip ? (L->mixed ? c32 : c64) : (L->mixed ? a32 : a64)).push_back(L);
         std::vector<int> st;
+        if (!c32.empty()) {
+            PFCHK(chip_run_batch<float>(c32, bs, m, st));
+            for (size_t i = 0; i < c32.size(); ++i) PFCHK(ls_after(*c32[i], st[i], !batched));
+            if (batched) PFCHK(batch_round_correct(c32, st, bs));
+        }
+        if (!c64.empty()) {
+            PFCHK(chip_run_batch<double>(c64, bs, m, st));
+            for (size_t i = 0; i < c64.size(); ++i) PFCHK(ls_after(*c64[i], st[i], !batched));
+        }
         if (!a32.empty()) {
             PFCHK(batch_krylov_run<float>(a32, members, bs, m, st));
             for (size_t i = 0; i < a32.size(); ++i) PFCHK(ls_after(*a32[i], st[i], !batched));
@@ -2206,6 +2501,7 @@ pf_status pf_grid_create(const pf_grid_desc *d, pf_grid **out)
     g->bcphi_mask = bp; g->bcpsi_mask = bs;
     for (int f = 0; f < 6; ++f) g->bcval[f] = d->bc_value[f];
     g->ustream = (hipStream_t)d->stream;
+    g->pinned_shape = g_nt_override || g_ppt_override || g_kz_override || g_depth_override;
     g->c64 = g->cb64 = g->cp64 = default_cfg(d->nx, d->ny, d->nz, 8);
     g->c32 = g->cb32 = g->cp32 = default_cfg(d->nx, d->ny, d->nz, 4);
     if (g->c64.lds > LDS_MAX || g->c32.lds > LDS_MAX) {
