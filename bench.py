@@ -207,14 +207,15 @@ def forms_batch(pf, torch, batch, value_s, reps=3):
     for name, prec, batched in (("batched_mixed", pf.PF_MIXED, True), ("sequential_fp64", pf.PF_FP64, False)):
         batch.solve(pf, torch, prec, batched)          # first use: FP32 workspaces and tuning
         times = []
-        if name == "batched_mixed":
-            pf.pf_timing_enable(1, 4)
         for _ in range(reps):
             t, infos = batch.solve(pf, torch, prec, batched)
             times.append(t)
         row = dict(seconds=sorted(times)[len(times) // 2], total_iters=sum(i["iters"] for i in infos),
                    max_rel_res=batch.max_rel_res(pf), fp64_fallbacks=sum(i["fp64_fallback"] for i in infos))
         if name == "batched_mixed":
+            for _ in range(2):   # the two-kernel iteration's step A (first its launch shapes)
+                pf.pf_timing_enable(1, 4)
+                batch.solve(pf, torch, prec, batched)
             tm = pf.pf_timing_read(pf.TIMING_BATCH_FP32)
             pf.pf_timing_enable(0, 1)
             row["step_a_fp32"] = dict(launches=tm["launches"], mean_us=tm["mean_ms"] * 1e3,
@@ -260,19 +261,14 @@ def forms_pf97(pf, torch, inputs):
         phi = torch.zeros(prob.N, dtype=torch.float64, device="cuda")
         pf.pf_nonlinear_solve(g, prm, phi)              # tuning, workspaces
         phi.zero_()
-        pf.pf_timing_enable(1, 16)
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         info = pf.pf_nonlinear_solve(g, prm, phi)
         torch.cuda.synchronize()
         sec = time.perf_counter() - t0
-        tm = pf.pf_timing_read(prec)
-        pf.pf_timing_enable(0, 1)
         phis[name] = phi
         out[name] = dict(seconds=sec, outer_iters=info["outer_iters"], lin_iters=info["total_lin_iters"],
-                         step_a_mean_us=tm["mean_ms"] * 1e3,
-                         step_a_effective_gbs_cache_resident=tm["bytes"] / tm["launches"] / (tm["mean_ms"] * 1e-3)
-                         / 1e9 if tm["launches"] else None)
+                         us_per_lin_iter=sec * 1e6 / max(1, info["total_lin_iters"]))
     out["mixed_vs_fp64_rel_l2"] = float(torch.linalg.vector_norm(phis["mixed"] - phis["fp64"])
                                         / torch.linalg.vector_norm(phis["fp64"]))
     out["mixed_speedup"] = out["fp64"]["seconds"] / out["mixed"]["seconds"]
@@ -838,7 +834,8 @@ def main():
     for w in range(args.warmup):
         t, infos = batch.solve(pf, torch, pf.PF_FP64, True)
         log(f"[bench] warmup {w}: {t:.3f} s, {sum(i['iters'] for i in infos)} iterations")
-    pf.pf_timing_enable(1, args.sample)
+    if args.pmc_run:   # counter runs look at the two-kernel iteration
+        pf.pf_timing_enable(1, args.sample)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for s_ in range(args.steps):
@@ -847,6 +844,15 @@ def main():
             f"max rel res {max(i['rel_res'] for i in infos):.2e}")
     torch.cuda.synchronize()
     elapsed = time.perf_counter() - t0
+    if not args.pmc_run:
+        # the timed steps run on chip; the HBM-bound kernel of the two-kernel
+        # iteration (larger grids, other fields) is timed on solves of its own,
+        # the first of which tunes its launch shapes
+        pf.pf_timing_enable(1, args.sample)
+        batch.solve(pf, torch, pf.PF_FP64, True)
+        pf.pf_timing_enable(1, args.sample)
+        t2, _ = batch.solve(pf, torch, pf.PF_FP64, True)
+        log(f"[bench] two-kernel iteration: {t2:.3f} s")
     tm = pf.pf_timing_read(pf.TIMING_BATCH_FP64)
     pf.pf_timing_enable(0, 1)
     sec_per_step = elapsed / args.steps
@@ -875,8 +881,8 @@ def main():
         "data": "synthetic",
         "config": {
             "workload": (f"batch_64: 64 linearised-PB systems 33^3..129^3 ({batch.unknowns:,} unknowns), each "
-                         "Jacobi-BiCGSTAB FP64 from x = 0 to true rel. residual 1e-10, batched (one launch per "
-                         "step kernel per iteration over all iterating members)"),
+                         "Jacobi-BiCGSTAB FP64 from x = 0 to true rel. residual 1e-10, batched (one launch for "
+                         "every member's Krylov run, vectors on chip)"),
             "members": len(batch.probs),
             "unknowns": batch.unknowns,
             "bicgstab_iters_total": total_iters,
@@ -887,8 +893,9 @@ def main():
         },
         "roofline": {
             "bound": "hbm",
-            "kernel": ("batched BiCGSTAB step A, FP64, palette form with the shift per class (previous x, "
-                       "r^ update + p^ update + v^ = D^-1 A p^ + 2 dots over every iterating member)"),
+            "kernel": ("batched BiCGSTAB step A of the two-kernel iteration, FP64, palette form with the shift per "
+                       "class (previous x, r^ update + p^ update + v^ = D^-1 A p^ + 2 dots over every iterating "
+                       "member), timed on a solve after the timed steps, which run on chip"),
             "achieved": achieved,
             "peak": PEAK_HBM_GBS,
             "unit": "GB/s",

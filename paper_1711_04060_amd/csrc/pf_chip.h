@@ -4,6 +4,7 @@
 #pragma once
 
 #include "pf_device.h"
+#include <stddef.h>
 
 namespace pfk {
 
@@ -11,6 +12,10 @@ constexpr int CH_NT = 512;      // threads per workgroup (tile)
 constexpr int CH_LP = 616;      // LDS elements per staged plane; the last one takes masked stores
 constexpr int CH_NQ = 5;        // sums per phase (at most)
 constexpr int CH_GMAX = 256;    // tiles of one system (one per CU)
+
+// bytes of the exchanged sums: two buffers of the tiles' and of the groups'
+// (16-byte words), and the tiles' XCD ids
+constexpr size_t CH_SUMS = 2 * CH_NQ * (CH_GMAX + 8) * 16 + CH_GMAX * 8;
 
 // xy halo nodes kept per thread
 constexpr int chip_halo_slots(int kz) { return kz <= 4 ? 1 : kz <= 8 ? 2 : 3; }
@@ -29,7 +34,7 @@ struct ChipGeom {
     int o[3], n[3];             // first unknown and their count per axis
     int c[3];
     int G = 0;
-    int fx = 0, fy = 0, fz = 0; // largest face of a tile normal to x, y, z
+    int fx = 0, fy = 0, fz = 0; // largest face of a tile normal to x, y, z, in whole cache lines
     int fstride = 0;            // exchange elements of a tile: 2 (fx + fy + fz)
 };
 
@@ -52,7 +57,7 @@ struct ChipSys {
     Scalars *sc;
     Scalars init;               // scalar block of the start
     void *face;                 // [2][G][fstride] exchanged boundary values (2 sizeof(T) bytes each)
-    void *sums;                 // [2][CH_NQ][G] exchanged partial sums (16 bytes each)
+    void *sums;                 // exchanged partial sums and XCD ids (CH_SUMS bytes)
     unsigned tag0;              // tag of phase 0; phases count up from it
 };
 

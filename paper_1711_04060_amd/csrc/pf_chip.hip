@@ -53,15 +53,18 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr int SC1 = 16;   // agent scope of a buffer access
 
-// Publish a value under a tag: {32 bits, tag} words.
+// Publish a value under a tag: {32 bits, tag} words.  SCOPE: SC1, or 0 where
+// the reader shares the writer's L2.
+template <int SCOPE>
 __device__ __forceinline__ void xput(__amdgpu_buffer_rsrc_t b, unsigned at, unsigned base, double v, unsigned tag)
 {
     const u32x2 w = __builtin_bit_cast(u32x2, v);
-    __builtin_amdgcn_raw_buffer_store_b128(u32x4{w.x, tag, w.y, tag}, b, at, base, SC1);
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4{w.x, tag, w.y, tag}, b, at, base, SCOPE);
 }
+template <int SCOPE>
 __device__ __forceinline__ void xput(__amdgpu_buffer_rsrc_t b, unsigned at, unsigned base, float v, unsigned tag)
 {
-    __builtin_amdgcn_raw_buffer_store_b64(u32x2{__builtin_bit_cast(unsigned, v), tag}, b, at, base, SC1);
+    __builtin_amdgcn_raw_buffer_store_b64(u32x2{__builtin_bit_cast(unsigned, v), tag}, b, at, base, SCOPE);
 }
 
 // A published value as read: the words, whether they have arrived under the
@@ -80,13 +83,15 @@ __device__ __forceinline__ bool xmiss(u32x2 w, unsigned tag) { return w.y != tag
 __device__ __forceinline__ double xval(u32x4 w) { return __builtin_bit_cast(double, u32x2{w.x, w.z}); }
 __device__ __forceinline__ float xval(u32x2 w) { return __builtin_bit_cast(float, w.x); }
 // The same without a tag.
+template <int SCOPE>
 __device__ __forceinline__ void xput_plain(__amdgpu_buffer_rsrc_t b, unsigned at, unsigned base, double v)
 {
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), b, at, base, SC1);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), b, at, base, SCOPE);
 }
+template <int SCOPE>
 __device__ __forceinline__ void xput_plain(__amdgpu_buffer_rsrc_t b, unsigned at, unsigned base, float v)
 {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), b, at, base, SC1);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), b, at, base, SCOPE);
 }
 __device__ __forceinline__ void xget_plain(__amdgpu_buffer_rsrc_t b, unsigned at, unsigned base, double &v)
 {
@@ -207,8 +212,9 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
     T *const ft = L + KZ * LP;
     T *const st = ft + FTAB;
     T *const PX = st + PAL_MAX;              // BIG: p^ of the own nodes
-    __shared__ double sred[4][CH_NQ], bred[NW][CH_NQ];
+    __shared__ double stot[4][CH_NQ], bred[NW][CH_NQ];
     __shared__ int sfail;
+    __shared__ unsigned snear;
 
     int si = 0, lb = blockIdx.x;
     if (nsys > 1) {
@@ -222,6 +228,7 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
     }
     const ChipSys<T> &S = table[si];
     const int nx = S.nx, ny = S.ny, nz = S.nz, P = S.P, G = S.ge.G;
+    lb = xcd_remap(lb, G);   // an XCD's tiles lie together
     const int cx = S.ge.c[0], cy = S.ge.c[1], cz = S.ge.c[2];
     const int tz = __builtin_amdgcn_readfirstlane(lb / (cx * cy)), trow = lb - tz * cx * cy;
     const int ty = __builtin_amdgcn_readfirstlane(trow / cx), tx = trow - ty * cx;
@@ -255,9 +262,11 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
     // pub[u] (DUMMY: a slot nobody reads)
     constexpr int FS = chip_face_slots(KZ);
     int pub[FS];
+    unsigned side[FS];   // the face: -x +x -y +y -z +z
 #pragma unroll
     for (int u = 0; u < FS; ++u) {
         int e = tid + u * NT, k = nk, q = 0;   // plane, index within the plane's staged cells
+        side[u] = e < 2 * fx ? (e >= fx) : e < bzlo ? 2 + (e >= 2 * fx + fy) : 4 + (e >= bzhi);
         if (e < 2 * fx) {
             const bool up = e >= fx;
             if (up) e -= fx;
@@ -496,10 +505,63 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
     };
 
     // exchange: two buffers of face values, then two of sums
-    const unsigned fbuf = (unsigned)(G * fs) * EB, sbuf = (unsigned)(CH_NQ * G) * 16u;
+    const unsigned fbuf = (unsigned)(G * fs) * EB;
     const auto xf = __builtin_amdgcn_make_buffer_rsrc(S.face, 0, (int)(2 * fbuf), 0x00027000);
-    const auto xs = __builtin_amdgcn_make_buffer_rsrc(S.sums, 0, (int)(2 * sbuf), 0x00027000);
+    // sums: two buffers of the tiles' (a row of GR words per group and
+    // quantity; or all tiles as one group), two of the groups', XCD ids
+    constexpr unsigned GR = CH_GMAX / 8, SB1 = 8 * CH_NQ * GR * 16, SB2 = CH_NQ * 8 * 16;
+    const auto xs = __builtin_amdgcn_make_buffer_rsrc(S.sums, 0, (int)(2 * SB1), 0x00027000);
+    const auto xg = __builtin_amdgcn_make_buffer_rsrc((char *)S.sums + 2 * SB1, 0, (int)(2 * SB2), 0x00027000);
+    const auto xi = __builtin_amdgcn_make_buffer_rsrc((char *)S.sums + 2 * (SB1 + SB2), 0, 8 * CH_GMAX, 0x00027000);
+    // Of more than 128 tiles, each group (the tiles xcd_remap gives one XCD)
+    // adds up first: its first tile takes the members' sums and publishes
+    // theirs, and every tile takes the eight groups'.  (All tiles reading all
+    // sums moved 3.7 MB an exchange and poll at 216 tiles: 14.0 us an iteration
+    // at 97^3, 12.3 this way; at 49^3 with 108 tiles it is 8.3 against 9.6,
+    // and with 16 planes a tile, where phases are long, 19.9 against 20.9 at
+    // 113^3.)
+    const bool two = !BIG && G > 128;
+    const int gper = G / 8, grem = G % 8, gcut = grem * (gper + 1);
+    const int grp = !two ? 0 : __builtin_amdgcn_readfirstlane(lb < gcut ? lb / (gper + 1) : grem + (lb - gcut) / gper);
+    const int gat = !two ? 0 : grp * gper + (grp < grem ? grp : grem);    // first tile of the group
+    const int gsz = !two ? G : gper + (grp < grem ? 1 : 0);
+    const unsigned grow = two ? GR : (unsigned)G;                                // words of a row
+    const unsigned gbase = (unsigned)grp * (CH_NQ * GR) * 16u;
     const unsigned tag0 = S.tag0;
+    // the neighbours on this XCD (bit per face): their values go through its
+    // L2 only (nearby tiles are, where the dispatcher deals the workgroups to
+    // the XCDs in turn; the ids are the hardware's own)
+    const unsigned xcc = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 15u;   // HW_REG_XCC_ID
+    unsigned near = 0;
+    if (tid < 64) {
+        if (tid == 0) __builtin_amdgcn_raw_buffer_store_b64(u32x2{xcc, tag0}, xi, (unsigned)lb * 8u, 0, SC1);
+        const int dn[6] = {tx > 0 ? -1 : 0, tx < cx - 1 ? 1 : 0, ty > 0 ? -cx : 0, ty < cy - 1 ? cx : 0,
+                           tz > 0 ? -cx * cy : 0, tz < cz - 1 ? cx * cy : 0};
+        // lanes 0..5: the face neighbours; from 8 on: the group's tiles
+        int d = two && tid >= 8 && tid - 8 < gsz ? gat + tid - 8 - lb : 0;
+#pragma unroll
+        for (int f = 0; f < 6; ++f) d = tid == f ? dn[f] : d;
+        u32x2 w;
+        for (int spin = 0;; ++spin) {
+            w = __builtin_amdgcn_raw_buffer_load_b64(xi, (unsigned)(lb + d) * 8u, 0, SC1);
+            if (!__any(w.y != tag0)) break;
+            if (spin >= CH_SPIN) {
+                sfail = 1;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(CH_SLEEP);
+            asm volatile("" ::: "memory");
+        }
+        const unsigned long long same = __ballot(w.x == xcc);
+        near = (unsigned)(same & 63u) | ((same >> 8) == (~0ull >> 8) && two ? 64u : 0u);   // bit 6: the whole group
+        if (tid == 0) snear = near;
+    }
+    __syncthreads();
+    if (sfail) return;
+    near = snear;
+    unsigned local = 0;   // bit u: slot u's reader is near
+#pragma unroll
+    for (int u = 0; u < FS; ++u) local |= ((near >> side[u]) & 1u) << u;
     // phase n: the tile's sums, and the boundary values of val, which takes
     // the staged planes' own cells (whole lines per wave go out)
     auto publish = [&](const int n, const T(&val)[KZ], auto &acc) {
@@ -518,7 +580,10 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
         if constexpr (!TAGGED) {
 #pragma unroll
             for (int u = 0; u < FS; ++u)
-                if (pub[u] != DUMMY) xput_plain(xf, (unsigned)(tid + u * NT) * EB, base, L[pub[u]]);
+                if (pub[u] != DUMMY) {
+                    const unsigned at = (unsigned)(tid + u * NT) * EB;
+                    xput_plain<SC1>(xf, at, base, L[pub[u]]);
+                }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's values are out
             __syncthreads();                                   // every wave's
         }
@@ -526,27 +591,61 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
             double s = bred[0][tid];
 #pragma unroll
             for (int w = 1; w < NW; ++w) s += bred[w][tid];
-            xput(xs, (unsigned)(tid * G + lb) * 16u, (n & 1) * sbuf, s, tag0 + n);
+            const unsigned at = (unsigned)(tid * grow + (lb - gat)) * 16u, sb = (n & 1) * SB1 + gbase;
+            if (near & 64u) xput<0>(xs, at, sb, s, tag0 + n);
+            else xput<SC1>(xs, at, sb, s, tag0 + n);
         }
         if constexpr (TAGGED) {
 #pragma unroll
             for (int u = 0; u < FS; ++u)
-                if (pub[u] != DUMMY) xput(xf, (unsigned)(tid + u * NT) * EB, base, L[pub[u]], tag0 + n);
+                if (pub[u] != DUMMY) {
+                    const unsigned at = (unsigned)(tid + u * NT) * EB;
+                    if ((local >> u) & 1u) xput<0>(xf, at, base, L[pub[u]], tag0 + n);
+                    else xput<SC1>(xf, at, base, L[pub[u]], tag0 + n);
+                }
         }
     };
     // wait for phase n: halo values into h, z, the grid's sums into tot;
     // false: gave up
     auto receive = [&](const int n, T(&h)[HS], T(&z)[2], auto &tot) -> bool {
         constexpr int NQ = sizeof(tot) / sizeof(double);
-        const unsigned base = (n & 1) * fbuf, sb = (n & 1) * sbuf, tag = tag0 + n;
+        const unsigned base = (n & 1) * fbuf, sb = (n & 1) * SB1 + gbase, tag = tag0 + n;
         using W = typename Word<T>::W;
         double s[NQ];
-        __builtin_amdgcn_s_sleep(BIG ? CH_SLEEPB0 : CH_SLEEP0);
-        const bool summer = tid < G;
+        const bool summers = tid < 64 || (!two && (tid & ~63) < G);   // uniform in a wave
+        // the sums of this tile's group into s (lane: tile), once
+        const bool summer = tid < gsz;   // (two: of the first wave only)
         const unsigned sat = (summer ? (unsigned)tid : 0u) * 16u;
-        const bool summers = (tid & ~63) < G;   // uniform: this wave takes sums
-        for (int spin = 0; TAGGED || summers; ++spin) {
+        auto group_sums = [&]() -> bool {
             u32x4 sw[NQ];
+            bool miss = false;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) xload(xs, sat, sb + (unsigned)q * grow * 16u, sw[q]);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                miss |= summer && xmiss(sw[q], tag);
+                s[q] = summer ? xval(sw[q]) : 0.0;
+            }
+            return miss;
+        };
+        if (two && tid < 64 && lb == gat) {
+            for (int spin = 0;; ++spin) {
+                if (!__any(group_sums())) break;
+                if (spin >= CH_SPIN) {
+                    sfail = 1;
+                    break;
+                }
+                asm volatile("" ::: "memory");   // every poll reads again
+            }
+            wave_sums<NQ>(s);
+            if (tid == 63 && !sfail) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) xput<SC1>(xg, (unsigned)(q * 8 + grp) * 16u, (n & 1) * SB2, s[q], tag);
+            }
+        }
+        __builtin_amdgcn_s_sleep(BIG ? CH_SLEEPB0 : CH_SLEEP0);
+        double gs = 0.0;   // two: lane 8 q + g holds quantity q of group g
+        for (int spin = 0; TAGGED || summers; ++spin) {
             W hw[HS], zw[2];
             bool miss = false;
             if constexpr (TAGGED) {
@@ -556,12 +655,14 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
                 xload(xf, zsrc_hi, base, zw[1]);
             }
             if (summers) {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) xload(xs, sat, sb + (unsigned)(q * G) * 16u, sw[q]);
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) {
-                    miss |= summer && xmiss(sw[q], tag);
-                    s[q] = summer ? xval(sw[q]) : 0.0;
+                if (two) {
+                    u32x4 w;
+                    const bool in = tid < 8 * NQ;
+                    xload(xg, (in ? (unsigned)tid : 0u) * 16u, (n & 1) * SB2, w);
+                    miss = in && xmiss(w, tag);
+                    gs = in ? xval(w) : 0.0;
+                } else {
+                    miss = group_sums();
                 }
             }
             if constexpr (TAGGED) {
@@ -583,10 +684,17 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
             asm volatile("" ::: "memory");   // every poll reads again
         }
         if (summers) {
-            wave_sums<NQ>(s);
-            if ((tid & 63) == 63) {
+            if (two) {
+                gs = dpp_add<0x111, 0xf>(gs);   // over the eight lanes of a quantity
+                gs = dpp_add<0x112, 0xf>(gs);
+                gs = dpp_add<0x114, 0xf>(gs);
+                if ((tid & 7) == 7 && tid < 8 * NQ) stot[0][tid >> 3] = gs;
+            } else {
+                wave_sums<NQ>(s);
+                if ((tid & 63) == 63) {
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) sred[tid >> 6][q] = s[q];
+                    for (int q = 0; q < NQ; ++q) stot[tid >> 6][q] = s[q];
+                }
             }
         }
         __syncthreads();
@@ -596,11 +704,11 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
             xget_plain(xf, zsrc_lo, base, z[0]);
             xget_plain(xf, zsrc_hi, base, z[1]);
         }
-        const int nw = (G + 63) >> 6;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            double a = sred[0][q];
-            for (int w = 1; w < nw; ++w) a += sred[w][q];
+            double a = stot[0][q];
+            if (!two)
+                for (int w = 1; w < (G + 63) >> 6; ++w) a += stot[w][q];
             tot[q] = uni(a);
         }
         if constexpr (!TAGGED) {
@@ -855,6 +963,8 @@ ChipGeom chip_partition(int nx, int ny, int nz, int neu, int gcap, int kzmax)
         if (u[a] < 1) return best;
     }
     gcap = gcap < CH_GMAX ? gcap : CH_GMAX;
+    // a face takes whole 128-byte lines: a line has one writer and one reader
+    auto pad = [](int e) { return (e + 31) / 32 * 32; };
     long bcost = -1;
     for (int cz = (u[2] + kzmax - 1) / kzmax; cz <= u[2] && cz <= gcap; ++cz) {
         const int bz = (u[2] + cz - 1) / cz;
@@ -866,7 +976,7 @@ ChipGeom chip_partition(int nx, int ny, int nz, int neu, int gcap, int kzmax)
                 const int bx = (u[0] + cx - 1) / cx;
                 if (bx * by > CH_NT || (cx > 1 && u[0] / cx < 2)) continue;
                 if ((bx + 2) * (by + 2) > CH_LP - 1 || 2 * (bx + by) * bz > chip_halo_slots(kz) * CH_NT) continue;
-                if (2 * ((bx + by) * bz + bx * by) > chip_face_slots(kz) * CH_NT) continue;
+                if (2 * (pad(by * bz) + pad(bx * bz) + pad(bx * by)) > chip_face_slots(kz) * CH_NT) continue;
                 const long rows = (bx * by + 255) / 256, planes = bz <= 4 ? (bz + 1) / 2 * 2 : (bz + 3) / 4 * (kz > 8 ? 8 : 4);
                 const long cost = (rows * planes * 24 + cx * cy * cz) * 4096 + 2 * (bx + by) * bz;
                 if (bcost >= 0 && cost >= bcost) continue;
@@ -875,7 +985,7 @@ ChipGeom chip_partition(int nx, int ny, int nz, int neu, int gcap, int kzmax)
                 for (int a = 0; a < 3; ++a) { best.o[a] = o[a]; best.n[a] = u[a]; }
                 best.c[0] = cx; best.c[1] = cy; best.c[2] = cz;
                 best.G = cx * cy * cz;
-                best.fx = by * bz; best.fy = bx * bz; best.fz = bx * by;
+                best.fx = pad(by * bz); best.fy = pad(bx * bz); best.fz = pad(bx * by);
                 best.fstride = 2 * (best.fx + best.fy + best.fz);
             }
         }

@@ -1158,13 +1158,26 @@ bool chip_fits(const LinSolve &L)
     return chip_geom(g, L.op.psi, chip_kzmax(L), pfk::CH_GMAX).KZ > 0;
 }
 
+pf_status ls_round_residual(LinSolve &L);
+
 // Start of the next Krylov run: nothing to do yet for an on-chip run.
 template <typename T>
 pf_status ls_start(LinSolve &L, double tol2, bool zero_x)
 {
     L.run_tol2 = tol2;
     L.chip = chip_fits<T>(L);
-    if (!L.chip) return krylov_start<T>(L.g, work_of<T>(L.g), L.rr, tol2, L.iter, L.o->max_iter, zero_x);
+    if (!L.chip) {
+        // launch shapes of the two-kernel iteration on its first use (timing
+        // them overwrites the Krylov vectors: the start is computed again)
+        pf_grid *g = L.g;
+        if (tuning_enabled() && (!g->tuned || (sizeof(T) == 4 && !g->tuned32))) {
+            PFCHK(tune<double>(g));
+            if (sizeof(T) == 4) PFCHK(tune<T>(g));
+            PFCHK(ls_round_residual(L));
+            PFCHK(sync(g));
+        }
+        return krylov_start<T>(g, work_of<T>(g), L.rr, tol2, L.iter, L.o->max_iter, zero_x);
+    }
     *L.g->hsc = krylov_init(L.rr, tol2, L.iter, std::min(L.o->max_iter, L.iter + CHIP_MAX_RUN));
     return PF_OK;
 }
@@ -1176,7 +1189,7 @@ pf_status chip_system(LinSolve &L, const pfk::ChipGeom &ge, int kz, pfk::ChipSys
 {
     pf_grid *g = L.g;
     Work<T> &w = work_of<T>(g);
-    const size_t nsum = (size_t)2 * pfk::CH_NQ * ge.G * 16;
+    const size_t nsum = (pfk::CH_SUMS + 255) & ~(size_t)255;
     const size_t nface = ((size_t)2 * ge.G * ge.fstride * 2 * sizeof(T) + 255) & ~(size_t)255;
     const size_t need = nsum + nface + (kz > 8 ? (size_t)ge.G * kz * pfk::CH_NT * sizeof(T) : 0);
     if (need > g->chip_xch_bytes) {
@@ -1388,12 +1401,6 @@ pf_status ls_init_launch(LinSolve &L)
     PFCHK(ensure_work<double>(g));
     L.mixed = L.o->precision == PF_MIXED;
     if (L.mixed) PFCHK(ensure_work<float>(g));
-    // launch shapes of the two-kernel iteration, where a run will use it
-    // (tuning overwrites the Krylov vectors, not b or x)
-    if (L.mixed ? !chip_fits<float>(L) : !chip_fits<double>(L)) {
-        PFCHK(tune<double>(g));
-        if (L.mixed) PFCHK(tune<float>(g));
-    }
     if (L.op.sigma) {   // sigma >= 0 on free rows, read back with ||b_lift||
         PFCHK(fill<int>(g, &g->sc->neg_shift, 0, 1));
         hipLaunchKernelGGL(pfk::k_check_shift, dim3(pw_blocks(g->N)), dim3(NT), 0, g->stream, g->N, L.op.sigma,
