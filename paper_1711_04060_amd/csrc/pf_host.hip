@@ -2845,6 +2845,17 @@ pf_status species_dev(const pf_pf_params *p, pfk::SpeciesDev *sp)
     }
     const double v0 = vsum / p->n_species;
     for (int i = 0; i < p->n_species; ++i) sp->p[i] = v[i] / v0;
+    // bounds of the steric iteration's remaining error: L' >= lo, L'' <= R^2 / 4
+    // and |L'''| <= R^3 / (6 sqrt 3) for weights on values p in [lo, hi] (1 is one)
+    double lo = 1.0, hi = 1.0;
+    for (int i = 0; i < p->n_species; ++i) {
+        lo = std::min(lo, sp->p[i]);
+        hi = std::max(hi, sp->p[i]);
+    }
+    const double R = hi - lo, k = R * R / (8.0 * lo);
+    sp->c2 = k;
+    // Halley: (L'' / 2L')^2 - L''' / 6L' and higher orders (twice covers them)
+    sp->c3 = 2.0 * (k * k + R * R * R / (36.0 * std::sqrt(3.0) * lo));
     if (sp->steric) {
         if (!(occ < 1.0)) return fail(PF_ERR_ARG, "bath volume fraction must be < 1 (Gamma_B > 0)");
         sp->lnGB = std::log(1.0 - occ);

@@ -1163,6 +1163,7 @@ struct SpeciesDev {
     double lncb[MAXSP];      // ln C_i^B
     double lnvcb[MAXSP];     // ln(v_i C_i^B)
     double p[MAXSP];         // v_i / v_0
+    double c2, c3;           // error left by a Newton / Halley step d: at most c2 d^2 / c3 |d|^3
 };
 
 // Steric potential S at potential phi: root of
@@ -1170,25 +1171,41 @@ struct SpeciesDev {
 // the void-fraction identity Gamma = Gamma_B e^S = 1 - sum_i v_i C_i.
 // L is convex and increasing in S; Newton's method started at the upper
 // bracket S = -ln Gamma_B (where L >= 0) descends monotonically to the root.
+// Near it (|L| L'' below half of L'^2) Halley's step replaces Newton's: L'' is
+// the variance of the p under the weights that L' already has.  The iteration
+// ends with the step after which the remaining error is below the rounding of
+// S: L' is at least min p, and L'' and L''' are the variance and the third
+// cumulant of values in [min p, max p], which bounds the error by c2 d^2 or
+// c3 |d|^3 (species_dev).  Bound by the exponentials, nsp + 1 a step.
 // Everything stays in the log domain: |z_i phi| reaches 10^3 at charged nodes.
+// NS: the number of species where it is known to the compiler (the
+// exponentials of a step then overlap), 0: read from sp.
+template <int NS>
 __device__ __forceinline__ double steric_root(double phi, const SpeciesDev &sp)
 {
+    const int n = NS ? NS : sp.nsp;
     double S = -sp.lnGB;
     for (int it = 0; it < 200; ++it) {
         double m = sp.lnGB + S;
-        for (int i = 0; i < sp.nsp; ++i) m = fmax(m, sp.lnvcb[i] - sp.z[i] * phi + sp.p[i] * S);
-        double w0 = exp(sp.lnGB + S - m);
-        double sum = w0, dsum = w0;
-        for (int i = 0; i < sp.nsp; ++i) {
-            const double w = exp(sp.lnvcb[i] - sp.z[i] * phi + sp.p[i] * S - m);
+#pragma unroll
+        for (int i = 0; i < n; ++i) m = fmax(m, sp.lnvcb[i] - sp.z[i] * phi + sp.p[i] * S);
+        const double w0 = exp(sp.lnGB + S - m);
+        double sum = w0, dsum = w0, qsum = w0;
+#pragma unroll
+        for (int i = 0; i < n; ++i) {
+            const double w = exp(sp.lnvcb[i] - sp.z[i] * phi + sp.p[i] * S - m), pw = sp.p[i] * w;
             sum += w;
-            dsum += sp.p[i] * w;
+            dsum += pw;
+            qsum += sp.p[i] * pw;
         }
         const double L = m + log(sum);
-        const double step = L * sum / dsum;
-        const double Sn = S - step;
-        if (!(fabs(Sn - S) > 4.0 * 2.220446049250313e-16 * fmax(1.0, fabs(S)))) return Sn;
-        S = Sn;
+        // over sum^2: L'^2 and L L''
+        const double d2 = dsum * dsum, lv = L * (qsum * sum - d2);
+        const bool near = fabs(lv) <= 0.5 * d2;
+        // Newton L / L', Halley 2 L L' / (2 L'^2 - L L'')
+        const double step = L * sum * (near ? 2.0 * dsum / (2.0 * d2 - lv) : 1.0 / dsum), d = fabs(step);
+        S -= step;
+        if (!((near ? sp.c3 * d : sp.c2) * (d * d) > 1.1102230246251565e-16 * fmax(1.0, fabs(S)))) return S;
     }
     return S;
 }
@@ -1196,13 +1213,15 @@ __device__ __forceinline__ double steric_root(double phi, const SpeciesDev &sp)
 // Fermi update at one solvent node of potential ph: rho_hat into rh,
 // lambda sum z_i^2 C_i (= -rho_hat' of Eq. (11)) into sg, the steric
 // potential into S, and C_i into conc[i*N + n] when conc is given.
-__device__ __forceinline__ void fermi_at(double ph, const SpeciesDev &sp, double &rh, double &sg, double &S,
-                                         double *conc, size_t n, size_t N)
+template <int NS>
+__device__ __forceinline__ void fermi_species(double ph, const SpeciesDev &sp, double &rh, double &sg, double &S,
+                                              double *conc, size_t n, size_t N)
 {
     rh = 0.0;
     sg = 0.0;
-    S = sp.steric ? steric_root(ph, sp) : 0.0;
-    for (int i = 0; i < sp.nsp; ++i) {
+    S = sp.steric ? steric_root<NS>(ph, sp) : 0.0;
+#pragma unroll
+    for (int i = 0; i < (NS ? NS : sp.nsp); ++i) {
         const double C = exp(sp.lncb[i] - sp.z[i] * ph + sp.p[i] * S);
         rh += sp.z[i] * C;
         sg += sp.z[i] * sp.z[i] * C;
@@ -1210,6 +1229,16 @@ __device__ __forceinline__ void fermi_at(double ph, const SpeciesDev &sp, double
     }
     rh *= sp.lam;
     sg *= sp.lam;
+}
+__device__ __forceinline__ void fermi_at(double ph, const SpeciesDev &sp, double &rh, double &sg, double &S,
+                                         double *conc, size_t n, size_t N)
+{
+    switch (sp.nsp) {   // uniform
+    case 2: fermi_species<2>(ph, sp, rh, sg, S, conc, n, N); break;
+    case 3: fermi_species<3>(ph, sp, rh, sg, S, conc, n, N); break;
+    case 4: fermi_species<4>(ph, sp, rh, sg, S, conc, n, N); break;
+    default: fermi_species<0>(ph, sp, rh, sg, S, conc, n, N); break;
+    }
 }
 
 // Fermi update at every node; zeros off the solvent.  Writes any of:
