@@ -1167,12 +1167,11 @@ pf_status ls_start(LinSolve &L, double tol2, bool zero_x)
     L.run_tol2 = tol2;
     L.chip = chip_fits<T>(L);
     if (!L.chip) {
-        // launch shapes of the two-kernel iteration on its first use (timing
-        // them overwrites the Krylov vectors: the start is computed again)
+        // an on-chip run was expected (set-up), or an FP32 run before this
+        // FP64 one: the start is computed again after the shapes were timed
         pf_grid *g = L.g;
-        if (tuning_enabled() && (!g->tuned || (sizeof(T) == 4 && !g->tuned32))) {
-            PFCHK(tune<double>(g));
-            if (sizeof(T) == 4) PFCHK(tune<T>(g));
+        if (tuning_enabled() && !(sizeof(T) == 8 ? g->tuned : g->tuned32)) {
+            PFCHK(tune<T>(g));
             PFCHK(ls_round_residual(L));
             PFCHK(sync(g));
         }
@@ -1279,9 +1278,12 @@ struct ChipBuf {
     int hcap = 0;
 } g_chipb;
 
-// Tile limit of a batch member: its share of the chip by unknowns, or the
-// fewest tiles that hold it where the whole batch does not fit at once (the
-// tiles of later members then start as those of earlier ones end).
+// Partition of a batch member: within its share of the chip by unknowns, or
+// (where the whole batch does not fit at once, and the tiles of later members
+// start as those of earlier ones end) from the fewest tiles that hold it.  As
+// many members of its size as fit side by side then divide the chip evenly:
+// 113^3 in its fewest 168 tiles would leave 88 CUs to wait, and runs faster
+// in 256.
 template <typename T>
 const pfk::ChipGeom &chip_batch_geom(const LinSolve &L, double total)
 {
@@ -1289,7 +1291,8 @@ const pfk::ChipGeom &chip_batch_geom(const LinSolve &L, double total)
     int cap = std::max(1, (int)(pfk::CH_GMAX * ((double)L.g->N / total)));
     for (;; cap = std::max(cap + 1, cap * 9 / 8)) {
         const pfk::ChipGeom &ge = chip_geom(L.g, L.op.psi, kz, std::min(cap, pfk::CH_GMAX));
-        if (ge.KZ > 0 || cap >= pfk::CH_GMAX) return ge;
+        if (ge.KZ > 0 || cap >= pfk::CH_GMAX)
+            return ge.KZ > 0 ? chip_geom(L.g, L.op.psi, kz, pfk::CH_GMAX / std::max(1, pfk::CH_GMAX / ge.G)) : ge;
     }
 }
 
@@ -1419,6 +1422,16 @@ pf_status ls_init_launch(LinSolve &L)
     // (not for the outer loop's own shift, the Fermi derivative, which
     // varies over the solvent)
     L.class_probe = L.op.sigma && L.op.sigma != g->sig && !L.op.psi && use_palette(g) && shift_class_enabled();
+    // launch shapes of the two-kernel iteration, where its runs will use them
+    // (timing them overwrites the Krylov vectors, not b or x); a shift that
+    // may turn out to be one value per class is taken for one here
+    L.op.sig_class = L.class_probe;
+    const bool chip = L.mixed ? chip_fits<float>(L) : chip_fits<double>(L);
+    L.op.sig_class = false;
+    if (!chip) {
+        PFCHK(tune<double>(g));
+        if (L.mixed) PFCHK(tune<float>(g));
+    }
     if (L.class_probe) {   // is sigma one value per palette class?  read back with ||b_lift||
         if (!g->smm) {
             PFCHK(dalloc(g, &g->smm, 2 * pfk::PAL_MAX));
