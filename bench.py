@@ -5,19 +5,19 @@ A step is one batched solve of the 64 linearised Poisson-Boltzmann systems
 (sizes 33^3 to 129^3, 49,173,256 unknowns, each the PF2 operator at
 phi_0 = 0 with its own charge set and bath), every member Jacobi-BiCGSTAB
 (Sec. 4, Table 3) in FP64 from x = 0 to true relative residual 1e-10, all
-members' iterations in shared launches (one launch per BiCGSTAB step kernel
-per iteration covering every member still iterating).  This is the largest
+members' Krylov runs in one launch with the vectors on chip.  This is the largest
 single-GPU workload of the benchmark set.  All inputs are resident in device
 memory before the timed region starts.
 
 The JSON line also carries:
   roofline      the batched BiCGSTAB step-A stencil kernel (the previous
                 iteration's x, r update, the p update and v = A p^ in one
-                pass over every iterating member), timed with HIP events on
-                the library's stream over every launch of the timed steps
-                (one chunk of iterations out of --sample, default 1: all of
-                them, whose graph launches then become direct launches with
-                dispatch-stamped events); algorithmic bytes per launch
+                pass over every iterating member) of the two-kernel
+                iteration, which larger grids use, timed with HIP events on
+                the library's stream on a solve of its own after the timed
+                steps (one chunk of iterations out of --sample, default 1:
+                all of them, as direct launches with dispatch-stamped
+                events); algorithmic bytes per launch
                 = 77 B per node of every member still iterating (reads s^,
                 p^, v^, t^, x in FP64, the coefficient's one-byte palette
                 index, which also selects the member's shift from its
@@ -249,9 +249,7 @@ def forms_ceiling(pf, torch, n=193 ** 3 + 1, reps=30):
 def forms_pf97(pf, torch, inputs):
     """Configuration 2: the full PF nonlinear solve on the 97^3 membrane
     (outer 1e-8, BiCGSTAB 1e-10), FP64 and with mixed-precision linear
-    solves.  Its ~100 MB working set stays in the 256 MB Infinity Cache, so
-    the step-A rate is an effective (cache-resident) GB/s, not an HBM
-    fraction."""
+    solves; the linear solves run on chip."""
     prob = inputs.membrane_pore(97)
     g = pf.grid_from_problem(prob)
     out = {"workload": "membrane_pore 97^3 (912,673 nodes): full PF solve, outer 1e-8, BiCGSTAB 1e-10"}

@@ -13,8 +13,8 @@
 //
 // Time per iteration against the two-kernel iteration (which reads and writes
 // every vector each time, or, on small grids, waits for its launches and
-// prologues): 33^3 17 -> 7.4 us, 65^3 24 -> 9.5 us, 97^3 35 -> 15 us, 113^3
-// 49 -> 20 us, 129^3 65 -> 21.5 us (FP64).
+// prologues), FP64 solves to 1e-12: 33^3 18.3 -> 7.7 us, 65^3 25.3 -> 9.2,
+// 97^3 35.2 -> 12.6, 113^3 48.6 -> 21.7, 129^3 71.2 -> 24.3.
 //
 // What bounds it: an iteration has two grid-wide dependencies (alpha; omega
 // and beta).  Each tile publishes its partial sums and the boundary values of
