@@ -56,7 +56,7 @@ struct ChipSys {
     T *xtile;                   // KZ = 16: [G][KZ][CH_NT], x while the run lasts
     Scalars *sc;
     Scalars init;               // scalar block of the start
-    void *face;                 // [2][G][fstride] exchanged boundary values (2 sizeof(T) bytes each)
+    void *face;                 // [2][G][fstride] exchanged boundary values (tagged: 2 sizeof(T) bytes each)
     void *sums;                 // exchanged partial sums and XCD ids (CH_SUMS bytes)
     unsigned tag0;              // tag of phase 0; phases count up from it
 };
@@ -64,6 +64,16 @@ struct ChipSys {
 // Partition for a grid of nx x ny x nz nodes (Neumann faces: bit f of neu), at
 // most gcap tiles and kzmax planes per tile; KZ = 0 when it does not fit.
 ChipGeom chip_partition(int nx, int ny, int nz, int neu, int gcap, int kzmax);
+
+// Device memory of a run by the instance of kz planes, in two blocks that
+// never trade places: `tagged` bytes of {value, tag} words (the sums, and up to
+// 8 planes the boundary values at `face`) whose readers take a word for an
+// arrived one by its tag, and `plain` bytes of values without tags (16 planes:
+// the boundary values at `face`, x of the tiles at `xtile`).
+struct ChipSpace {
+    size_t tagged, plain, face, xtile;
+};
+ChipSpace chip_space(const ChipGeom &ge, int kz, size_t elem);
 
 // Dynamic LDS of a workgroup.
 size_t chip_lds(int kz, size_t elem);

@@ -29,7 +29,12 @@
 // Buffers: phase n uses buffer n & 1.  A tile writes phase n + 2 after it has
 // received every sum of phase n + 1, which each tile publishes after it has
 // read phase n.  Tags are never used twice on the same buffers (the host
-// counts them per grid).
+// counts them per grid), and the words that hold tags hold nothing else: every
+// odd 32-bit word of the tagged block is a tag, in FP64 and FP32 and whatever
+// the partition, and values without tags lie in a block of their own
+// (chip_space).  In one block, a 16-plane run's plain values would stay behind
+// where a later run looks for tags, and a plain FP32 value is a tag's bit
+// pattern sooner or later.
 //
 // Every wait is bounded (CH_SPIN polls).  A tile that gives up leaves without
 // writing x or the scalars, and so do all others (no tile can finish without
@@ -945,6 +950,22 @@ __global__ __launch_bounds__(256) void k_chip_start(const ChipSys<T> *table)
 size_t chip_lds(int kz, size_t elem)
 {
     return ((size_t)kz * CH_LP + FTAB + PAL_MAX + (kz > 8 ? (size_t)kz * CH_NT : 0)) * elem;
+}
+
+ChipSpace chip_space(const ChipGeom &ge, int kz, size_t elem)
+{
+    auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    const size_t values = (size_t)2 * ge.G * ge.fstride;   // two buffers of boundary values
+    ChipSpace m{};
+    if (kz <= 8) {
+        m.face = al(CH_SUMS);
+        m.tagged = m.face + al(values * 2 * elem);
+    } else {
+        m.tagged = al(CH_SUMS);
+        m.xtile = al(values * elem);
+        m.plain = m.xtile + (size_t)ge.G * kz * CH_NT * elem;
+    }
+    return m;
 }
 
 // Among the partitions that fit, the one of least cost: a tile's time for its

@@ -215,8 +215,10 @@ struct pf_grid {
     bool tuned = false, tuned32 = false;
     std::map<std::tuple<int, int, int>, pfk::ChipGeom> chip_geoms;   // per (PF1, planes per tile, tile limit)
     void *chip_table = nullptr;        // the system of a single run
-    char *chip_xch = nullptr;          // exchange buffers
+    char *chip_xch = nullptr;          // tagged exchange words (nothing else is ever written there)
     size_t chip_xch_bytes = 0;
+    char *chip_plain = nullptr;        // values without tags: boundary values and x of 16-plane tiles
+    size_t chip_plain_bytes = 0;
     unsigned chip_tag = 0;             // next unused exchange tag (0: buffers not cleared yet)
 
     // nonlinear state
@@ -1188,13 +1190,15 @@ pf_status chip_system(LinSolve &L, const pfk::ChipGeom &ge, int kz, pfk::ChipSys
 {
     pf_grid *g = L.g;
     Work<T> &w = work_of<T>(g);
-    const size_t nsum = (pfk::CH_SUMS + 255) & ~(size_t)255;
-    const size_t nface = ((size_t)2 * ge.G * ge.fstride * 2 * sizeof(T) + 255) & ~(size_t)255;
-    const size_t need = nsum + nface + (kz > 8 ? (size_t)ge.G * kz * pfk::CH_NT * sizeof(T) : 0);
-    if (need > g->chip_xch_bytes) {
-        PFCHK(dalloc(g, &g->chip_xch, need));
-        g->chip_xch_bytes = need;
+    const pfk::ChipSpace m = pfk::chip_space(ge, kz, sizeof(T));
+    if (m.tagged > g->chip_xch_bytes) {
+        PFCHK(dalloc(g, &g->chip_xch, m.tagged));
+        g->chip_xch_bytes = m.tagged;
         g->chip_tag = 0;
+    }
+    if (m.plain > g->chip_plain_bytes) {
+        PFCHK(dalloc(g, &g->chip_plain, m.plain));
+        g->chip_plain_bytes = m.plain;
     }
     // tags of this run: never used before on these buffers, which are cleared
     // when the count starts again (tag 0 is never used)
@@ -1219,8 +1223,8 @@ pf_status chip_system(LinSolve &L, const pfk::ChipGeom &ge, int kz, pfk::ChipSys
     S.sc = g->sc;
     S.init = *g->hsc;
     S.sums = g->chip_xch;
-    S.face = g->chip_xch + nsum;
-    S.xtile = reinterpret_cast<T *>(g->chip_xch + nsum + nface);
+    S.face = (m.plain ? g->chip_plain : g->chip_xch) + m.face;
+    S.xtile = m.plain ? reinterpret_cast<T *>(g->chip_plain + m.xtile) : nullptr;
     S.tag0 = g->chip_tag;
     g->chip_tag += RUN_TAGS;
     return PF_OK;
