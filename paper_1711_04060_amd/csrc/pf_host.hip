@@ -1117,7 +1117,7 @@ int chip_form(const LinSolve &L)
 }
 
 // Planes per tile: the instances with 16 keep two palette classes per node
-// and have no registers left for a shift of its own.
+// (one bit each) and have no registers left for a shift of its own.
 int chip_kzmax(const LinSolve &L)
 {
     if (L.op.psi) return 16;
@@ -1189,6 +1189,7 @@ template <typename T>
 pf_status chip_system(LinSolve &L, const pfk::ChipGeom &ge, int kz, pfk::ChipSys<T> &S)
 {
     pf_grid *g = L.g;
+    if (kz > chip_kzmax(L)) return fail(PF_ERR_DEVICE, "on-chip instance of %d planes cannot hold this operator", kz);
     Work<T> &w = work_of<T>(g);
     const pfk::ChipSpace m = pfk::chip_space(ge, kz, sizeof(T));
     if (m.tagged > g->chip_xch_bytes) {
@@ -1300,9 +1301,11 @@ const pfk::ChipGeom &chip_batch_geom(const LinSolve &L, double total)
     }
 }
 
-// On-chip runs of several systems in one launch per kernel form.  Tiles are
-// dispatched in order, so the earliest unfinished system always has all of
-// its tiles on the chip.
+// On-chip runs of several systems in one launch per kernel form and limit of
+// planes per tile (the launch's instance is the largest any member needs, and
+// an instance with 16 planes cannot hold the classes of a field of more than
+// two values).  Tiles are dispatched in order, so the earliest unfinished
+// system always has all of its tiles on the chip.
 template <typename T>
 pf_status chip_run_batch(std::vector<LinSolve *> &act, hipStream_t stream, int m, std::vector<int> &status)
 {
@@ -1312,7 +1315,8 @@ pf_status chip_run_batch(std::vector<LinSolve *> &act, hipStream_t stream, int m
     for (int i = 0; i < n; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
         const int fa = chip_form(*act[a]), fb = chip_form(*act[b]);
-        return fa != fb ? fa < fb : act[a]->g->N > act[b]->g->N;
+        const int ka = chip_kzmax(*act[a]), kb = chip_kzmax(*act[b]);
+        return fa != fb ? fa < fb : ka != kb ? ka > kb : act[a]->g->N > act[b]->g->N;
     });
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t szT = al(sizeof(pfk::ChipSys<T>) * n), szF = al(sizeof(int) * (2 * n + 1)), szP = al(sizeof(void *) * n);
@@ -1334,16 +1338,16 @@ pf_status chip_run_batch(std::vector<LinSolve *> &act, hipStream_t stream, int m
     auto *hgather = reinterpret_cast<Scalars *>(hb + up);
     double total = 0;
     for (const LinSolve *L : act) total += (double)L->g->N;
-    struct Launch { int form, kz, at, n, tiles, foff; };
+    struct Launch { int form, lim, kz, at, n, tiles, foff; };
     std::vector<Launch> ls;
     std::vector<const pfk::ChipGeom *> geo(n);
     int foff = 0;
     for (int i = 0; i < n; ++i) {
         geo[i] = &chip_batch_geom<T>(*act[order[i]], total);
-        const int form = chip_form(*act[order[i]]);
-        if (ls.empty() || ls.back().form != form) {
+        const int form = chip_form(*act[order[i]]), lim = chip_kzmax(*act[order[i]]);
+        if (ls.empty() || ls.back().form != form || ls.back().lim != lim) {
             if (!ls.empty()) ++foff;
-            ls.push_back(Launch{form, 0, i, 0, 0, foff});
+            ls.push_back(Launch{form, lim, 0, i, 0, 0, foff});
             hfirst[foff] = 0;
         }
         Launch &b = ls.back();

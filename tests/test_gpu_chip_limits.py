@@ -1,0 +1,41 @@
+"""Limits of the on-chip Krylov runs: what an instance of the kernel holds,
+and what happens when a run cannot have the chip, its memory or its time.
+
+Bars as in the parity tests: 1e-9 (FP64, stop 1e-12), 1e-8 (mixed, 1e-10).
+"""
+import pytest
+
+from test_gpu_chip import D, _blocks, _pf, _rel, _solve, dev
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _opts(pf, mixed, **kw):
+    return pf.pf_lin_opts_default(rel_tol=1e-10 if mixed else 1e-12,
+                                  precision=pf.PF_MIXED if mixed else pf.PF_FP64, **kw)
+
+
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("kind", ["none", "class"])
+def test_batch_of_fields_with_different_numbers_of_values(kind, mixed):
+    """A two-valued member of 16 planes per tile beside members of three and
+    four values, whose classes do not fit that instance: each iterates on its
+    own operator, so it takes the iterations and refinements it takes alone, but
+    for rounding (another partition adds up in another order: a few iterations,
+    or one restart from a true residual just above the stop)."""
+    pf = _pf()
+    made = [_blocks(*s, (D,) * 6, v, seed=9 + v) for s, v in
+            (((113, 113, 113), 2), ((33, 35, 37), 4), ((49, 50, 47), 3), ((41, 33, 29), 2))]
+    grids = [pf.grid_from_problem(m[0]) for m in made]
+    sig = [dev(m[1][kind]) for m in made]
+    bs = [dev(m[2]) for m in made]
+    xs = [torch.zeros_like(b) for b in bs]
+    print("batch", kind, mixed, flush=True)
+    infos = pf.pf_linear_solve_batch(grids, sig, bs, xs, _opts(pf, mixed, max_iter=4000))
+    for m, s, b, x, info in zip(made, sig, bs, xs, infos):
+        g = pf.grid_from_problem(m[0])
+        one = pf.pf_linear_solve(g, s, b, torch.zeros_like(b), _opts(pf, mixed, max_iter=4000))
+        assert info["status"] == 0 and info["fp64_fallback"] == one["fp64_fallback"]
+        assert info["iters"] <= 1.5 * one["iters"] and info["refinements"] <= one["refinements"] + 1
+        assert _rel(x.cpu().numpy(), _solve(pf, g, s, b, mixed, chip=False)) <= (1e-8 if mixed else 1e-9)
