@@ -12,6 +12,7 @@ constexpr int CH_NT = 512;      // threads per workgroup (tile)
 constexpr int CH_LP = 616;      // LDS elements per staged plane; the last one takes masked stores
 constexpr int CH_NQ = 5;        // sums per phase (at most)
 constexpr int CH_GMAX = 256;    // tiles of one system (one per CU)
+constexpr int CH_SPIN = 1 << 21;   // polls of one wait before a tile gives up
 
 // bytes of the exchanged sums: two buffers of the tiles' and of the groups'
 // (16-byte words), and the tiles' XCD ids
@@ -59,6 +60,7 @@ struct ChipSys {
     void *face;                 // [2][G][fstride] exchanged boundary values (tagged: 2 sizeof(T) bytes each)
     void *sums;                 // exchanged partial sums and XCD ids (CH_SUMS bytes)
     unsigned tag0;              // tag of phase 0; phases count up from it
+    int spin;                   // polls of one wait before a tile gives up
 };
 
 // Partition for a grid of nx x ny x nz nodes (Neumann faces: bit f of neu), at

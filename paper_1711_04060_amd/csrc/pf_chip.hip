@@ -36,16 +36,17 @@
 // where a later run looks for tags, and a plain FP32 value is a tag's bit
 // pattern sooner or later.
 //
-// Every wait is bounded (CH_SPIN polls).  A tile that gives up leaves without
-// writing x or the scalars, and so do all others (no tile can finish without
-// it); the caller finds the stop state unchanged and runs the two-kernel
-// iteration instead.  All tiles decide from the same sums in the same order,
-// so they leave in the same phase.
+// Every wait is bounded (spin polls).  A tile that gives up says so in the
+// scalar block and leaves without writing x; the others, which wait for it in
+// their turn, do the same, except where it gave up in the run's last phase: its
+// own values are out by then, so others may receive everything, stop and write
+// their part of x.  The caller therefore looks at gave_up before the stop
+// state, takes x for one of mixed origin, and starts the two-kernel iteration
+// from its true residual.  Tiles that do not give up decide from the same sums
+// in the same order, so they leave in the same phase.
 #include "pf_chip.h"
 
 namespace pfk {
-
-constexpr int CH_SPIN = 1 << 21;
 
 // Pauses (units of 64 cycles) before a tile's first poll and between polls:
 // polls that come before the others' values compete with them for the fabric
@@ -232,6 +233,7 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
         lb -= first[si];
     }
     const ChipSys<T> &S = table[si];
+    const int spin_max = S.spin;
     const int nx = S.nx, ny = S.ny, nz = S.nz, P = S.P, G = S.ge.G;
     lb = xcd_remap(lb, G);   // an XCD's tiles lie together
     const int cx = S.ge.c[0], cy = S.ge.c[1], cz = S.ge.c[2];
@@ -550,7 +552,7 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
         for (int spin = 0;; ++spin) {
             w = __builtin_amdgcn_raw_buffer_load_b64(xi, (unsigned)(lb + d) * 8u, 0, SC1);
             if (!__any(w.y != tag0)) break;
-            if (spin >= CH_SPIN) {
+            if (spin >= spin_max) {
                 sfail = 1;
                 break;
             }
@@ -562,7 +564,13 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
         if (tid == 0) snear = near;
     }
     __syncthreads();
-    if (sfail) return;
+    auto give_up = [&]() {
+        if (tid == 0) __hip_atomic_store(&S.sc->gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (sfail) {
+        give_up();
+        return;
+    }
     near = snear;
     unsigned local = 0;   // bit u: slot u's reader is near
 #pragma unroll
@@ -636,7 +644,7 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
         if (two && tid < 64 && lb == gat) {
             for (int spin = 0;; ++spin) {
                 if (!__any(group_sums())) break;
-                if (spin >= CH_SPIN) {
+                if (spin >= spin_max) {
                     sfail = 1;
                     break;
                 }
@@ -681,7 +689,7 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
                 z[1] = zhi_in ? xval(zw[1]) : T(0);
             }
             if (!__any(miss)) break;
-            if (spin >= CH_SPIN) {
+            if (spin >= spin_max) {
                 sfail = 1;
                 break;
             }
@@ -759,7 +767,10 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
             T ht[HS], zt[2] = {T(0), T(0)};
 #pragma unroll
             for (int u = 0; u < HS; ++u) ht[u] = T(0);
-            if (!receive(ph - 1, ht, zt, tot)) return;
+            if (!receive(ph - 1, ht, zt, tot)) {
+                give_up();
+                return;
+            }
             const FinB f = fin_b(&sc, tot, 0);
             if (f.update) {
                 iter = f.iter;
@@ -842,7 +853,10 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
         ++ph;
         // ---- step B: s^ = r^ - alpha v^, t^ = D^-1 A s^
         double tot2[2];
-        if (!receive(ph - 1, hv, zv, tot2)) return;
+        if (!receive(ph - 1, hv, zv, tot2)) {
+            give_up();
+            return;
+        }
         rr = tot2[1];
         double alpha = 0.0;
         if (!finite(tot2[0]) || !finite(rr)) stop = ST_NONFINITE;

@@ -31,6 +31,7 @@ struct Scalars {
     int fresh;         // 1 from a (re)start until step B of the first iteration
     int neg_shift;     // set when a free row of the operator has sigma < 0
     int shift_class;   // set when sigma is one value per palette class on the free rows
+    int gave_up;       // set by a tile of an on-chip run that stopped waiting for the others
 };
 enum { ST_RUN = 0, ST_CONV = 1, ST_RESTART = 3, ST_NONFINITE = 4, ST_MAXIT = 5 };
 

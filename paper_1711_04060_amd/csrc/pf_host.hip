@@ -1183,6 +1183,14 @@ pf_status ls_start(LinSolve &L, double tol2, bool zero_x)
     return PF_OK;
 }
 
+// Polls of one wait of an on-chip run (PF_CHIP_SPIN: a small limit makes tiles
+// give up, for tests).
+int chip_spin()
+{
+    const char *e = getenv("PF_CHIP_SPIN");
+    return e ? std::max(0, atoi(e)) : pfk::CH_SPIN;
+}
+
 // Table entry of a run of L in the partition ge by the kernel instance of kz
 // planes; the exchange buffers grow to it.
 template <typename T>
@@ -1227,6 +1235,7 @@ pf_status chip_system(LinSolve &L, const pfk::ChipGeom &ge, int kz, pfk::ChipSys
     S.face = (m.plain ? g->chip_plain : g->chip_xch) + m.face;
     S.xtile = m.plain ? reinterpret_cast<T *>(g->chip_plain + m.xtile) : nullptr;
     S.tag0 = g->chip_tag;
+    S.spin = chip_spin();
     g->chip_tag += RUN_TAGS;
     return PF_OK;
 }
@@ -1239,13 +1248,22 @@ std::mutex g_chip_mu[64];
 template <typename T>
 pf_status krylov_run(pf_grid *g, const OpDesc &op, Work<T> &w, int m_fixed, int *status, bool adaptive);
 
-// The tiles of an on-chip run gave up waiting: the same run by the
-// two-kernel iteration, from the start vectors it left untouched.
+pf_status ls_round_launch(LinSolve &L);
+
+// Tiles of an on-chip run gave up waiting: the two-kernel iteration from the
+// true residual of what is in x.  (An FP32 run solves for a correction, which
+// starts from zero again; in FP64 some tiles may have written their part of x,
+// any of which is a start as good as another.)
 template <typename T>
 pf_status chip_gave_up(LinSolve &L, int m, int *status)
 {
     pf_grid *g = L.g;
     g->chip_off = true;
+    if (getenv("PF_LOG"))
+        fprintf(stderr, "[pf] on-chip run of %dx%dx%d gave up waiting\n", g->nx, g->ny, g->nz);
+    PFCHK(ls_round_launch(L));
+    PFCHK(sync(g));
+    L.rr = g->hsc->red[0];
     PFCHK(krylov_start<T>(g, work_of<T>(g), L.rr, L.run_tol2, L.iter, L.o->max_iter, sizeof(T) == 4));
     return krylov_run<T>(g, L.op, work_of<T>(g), m, status, L.o->check_every == 0);
 }
@@ -1270,7 +1288,7 @@ pf_status chip_run(LinSolve &L, int m, int *status)
         PFCHK(read_scalars(g));
     }
     *status = g->hsc->stop;
-    if (*status == pfk::ST_RUN) return chip_gave_up<T>(L, m, status);
+    if (g->hsc->gave_up) return chip_gave_up<T>(L, m, status);
     return PF_OK;
 }
 
@@ -1380,7 +1398,7 @@ pf_status chip_run_batch(std::vector<LinSolve *> &act, hipStream_t stream, int m
         status[order[i]] = hgather[i].stop;
     }
     for (int i = 0; i < n; ++i)
-        if (status[i] == pfk::ST_RUN) PFCHK(chip_gave_up<T>(*act[i], m, &status[i]));
+        if (act[i]->g->hsc->gave_up) PFCHK(chip_gave_up<T>(*act[i], m, &status[i]));
     return PF_OK;
 }
 

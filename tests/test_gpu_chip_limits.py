@@ -39,3 +39,31 @@ def test_batch_of_fields_with_different_numbers_of_values(kind, mixed):
         assert info["status"] == 0 and info["fp64_fallback"] == one["fp64_fallback"]
         assert info["iters"] <= 1.5 * one["iters"] and info["refinements"] <= one["refinements"] + 1
         assert _rel(x.cpu().numpy(), _solve(pf, g, s, b, mixed, chip=False)) <= (1e-8 if mixed else 1e-9)
+
+
+# polls of a wait: 0 gives up before the run, the others at a late neighbour
+# somewhere in it, not necessarily in every tile
+@pytest.mark.parametrize("spin", [0, 1, 2, 4, 12])
+@pytest.mark.parametrize("mixed", [False, True])
+def test_run_that_gives_up_waiting_is_done_again(spin, mixed, monkeypatch, capfd):
+    """Tiles of 4 planes, of 8 with sums in two levels, and of 16, alone and as
+    a batch: with few polls allowed, tiles leave the run (every kernel ends by
+    itself), and the solve gives the same solution by the two-kernel
+    iteration, whatever part of x was written."""
+    pf = _pf()
+    made = [_blocks(*s, (D,) * 6, 2, seed=3 + i) for i, s in enumerate([(33, 35, 37), (97, 95, 97), (113, 105, 113)])]
+    bs = [dev(m[2]) for m in made]
+    refs = [_solve(pf, pf.grid_from_problem(m[0]), None, b, mixed, chip=False) for m, b in zip(made, bs)]
+    monkeypatch.setenv("PF_LOG", "1")
+    monkeypatch.setenv("PF_CHIP_SPIN", str(spin))
+    bar = 1e-8 if mixed else 1e-9
+    for m, b, ref in zip(made, bs, refs):
+        print("alone", m[0].nx, spin, mixed, flush=True)
+        assert _rel(_solve(pf, pf.grid_from_problem(m[0]), None, b, mixed), ref) <= bar
+    print("batch", spin, mixed, flush=True)
+    xs = [torch.zeros_like(b) for b in bs]
+    infos = pf.pf_linear_solve_batch([pf.grid_from_problem(m[0]) for m in made], [None] * 3, bs, xs, _opts(pf, mixed))
+    for x, ref, info in zip(xs, refs, infos):
+        assert info["status"] == 0 and _rel(x.cpu().numpy(), ref) <= bar
+    if spin == 0:
+        assert capfd.readouterr().err.count("gave up waiting") == 6
