@@ -12,7 +12,7 @@ constexpr int CH_NT = 512;      // threads per workgroup (tile)
 constexpr int CH_LP = 616;      // LDS elements per staged plane; the last one takes masked stores
 constexpr int CH_NQ = 5;        // sums per phase (at most)
 constexpr int CH_GMAX = 256;    // tiles of one system (one per CU)
-constexpr int CH_SPIN = 1 << 21;   // polls of one wait before a tile gives up
+constexpr int CH_SPIN = 1 << 19;   // polls of one wait before a tile gives up
 
 // bytes of the exchanged sums: two buffers of the tiles' and of the groups'
 // (16-byte words), and the tiles' XCD ids

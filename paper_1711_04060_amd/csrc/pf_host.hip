@@ -211,7 +211,7 @@ struct pf_grid {
 
     // on-chip Krylov runs (pf_chip.h)
     bool pinned_shape = false;         // created under a launch override: the two-kernel iteration only
-    bool chip_off = false;             // an on-chip run gave up waiting: the two-kernel iteration from then on
+    int chip_cap = -1;                 // tiles that can wait for each other on this grid's stream (-1: not asked yet)
     bool tuned = false, tuned32 = false;
     std::map<std::tuple<int, int, int>, pfk::ChipGeom> chip_geoms;   // per (PF1, planes per tile, tile limit)
     void *chip_table = nullptr;        // the system of a single run
@@ -1142,22 +1142,89 @@ const pfk::ChipGeom &chip_geom(pf_grid *g, bool psi, int kzmax, int gcap)
     return it->second;
 }
 
+// Tiles of an on-chip run wait for each other, so all of them have to be on
+// the device together: at most one per compute unit it has (PF_CHIP_CUS: fewer,
+// for tests).  None on a stream that is masked off some of them, where the
+// tiles' share of each XCD is not known.  (A mask that the runtime does not
+// report, or another process, shows as a run that gives up.)
+int chip_cap(pf_grid *g)
+{
+    if (g->chip_cap < 0) {
+        int cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, g->device) != hipSuccess) cus = 0;
+        uint32_t mask[64] = {};
+        if (hipExtStreamGetCUMask(g->stream, 64, mask) == hipSuccess) {
+            int on = 0;
+            for (uint32_t w : mask) on += __builtin_popcount(w);
+            if (on > 0 && on < cus) cus = 0;
+        }
+        (void)hipGetLastError();
+        if (const char *e = getenv("PF_CHIP_CUS")) cus = std::min(cus, std::max(0, atoi(e)));
+        g->chip_cap = std::min(cus, pfk::CH_GMAX);
+    }
+    return g->chip_cap;
+}
+
+// After a run that gave up waiting (something else holds compute units: most
+// likely another process that waits in the same way), the device's next 64 runs
+// keep to the two-kernel iteration, four times as many after each further
+// time, up to 2^18; runs that end well take the steps back.  A give-up costs
+// about half a second, a run on chip saves about a millisecond.
+struct ChipDevice {
+    std::mutex run;   // one on-chip launch at a time, held until it has ended (other work only delays it)
+    std::mutex mu;
+    int strikes = 0;
+    long pause = 0;
+} g_chip_dev[64];
+
+ChipDevice &chip_device(const pf_grid *g) { return g_chip_dev[g->device & 63]; }
+
+// PF_CHIP: 0 no on-chip runs (for comparisons), 1 no pauses after a give-up
+// (for tests).
+char chip_switch()
+{
+    const char *e = getenv("PF_CHIP");
+    return e ? e[0] : 0;
+}
+
+// Is the device open to an on-chip run?  (take: this is one.)
+bool chip_open(const pf_grid *g, bool take)
+{
+    if (chip_switch() == '1') return true;
+    ChipDevice &d = chip_device(g);
+    std::lock_guard<std::mutex> lock(d.mu);
+    if (d.pause == 0) return true;
+    if (take) --d.pause;
+    return false;
+}
+
+void chip_ended(const pf_grid *g, bool gave_up)
+{
+    if (chip_switch() == '1') return;
+    ChipDevice &d = chip_device(g);
+    std::lock_guard<std::mutex> lock(d.mu);
+    if (gave_up) {
+        d.strikes = std::min(d.strikes + 1, 7);
+        d.pause = 16L << (2 * d.strikes);
+    } else if (d.strikes > 0) {
+        --d.strikes;
+    }
+}
+
 // Krylov runs of this solve go on chip where the unknowns fit it.  Not where
 // the caller asks for something of the two-kernel iteration itself: launch
 // shapes (pf_set_launch, PF_BATCH_POLICY), kernel timing, a status read
-// every check_every iterations; nor for fields without a palette.  PF_CHIP=0
-// turns it off (for comparisons).
+// every check_every iterations; nor for fields without a palette.
 template <typename T>
 bool chip_fits(const LinSolve &L)
 {
     pf_grid *g = L.g;
-    if (g->pinned_shape || g->chip_off || g_timing.enabled || L.o->check_every > 0) return false;
+    if (g->pinned_shape || g_timing.enabled || L.o->check_every > 0) return false;
     if (g_nt_override || g_ppt_override || g_kz_override || g_depth_override) return false;
     if (!L.op.psi && !use_palette(g)) return false;
-    const char *e = getenv("PF_CHIP");
-    if (e && e[0] == '0') return false;
+    if (chip_switch() == '0') return false;
     if (getenv("PF_BATCH_POLICY")) return false;
-    return chip_geom(g, L.op.psi, chip_kzmax(L), pfk::CH_GMAX).KZ > 0;
+    return chip_geom(g, L.op.psi, chip_kzmax(L), chip_cap(g)).KZ > 0;
 }
 
 pf_status ls_round_residual(LinSolve &L);
@@ -1167,7 +1234,7 @@ template <typename T>
 pf_status ls_start(LinSolve &L, double tol2, bool zero_x)
 {
     L.run_tol2 = tol2;
-    L.chip = chip_fits<T>(L);
+    L.chip = chip_fits<T>(L) && chip_open(L.g, true);
     if (!L.chip) {
         // an on-chip run was expected (set-up), or an FP32 run before this
         // FP64 one: the start is computed again after the shapes were timed
@@ -1183,18 +1250,22 @@ pf_status ls_start(LinSolve &L, double tol2, bool zero_x)
     return PF_OK;
 }
 
-// Polls of one wait of an on-chip run (PF_CHIP_SPIN: a small limit makes tiles
-// give up, for tests).
-int chip_spin()
+// Polls of one wait of an on-chip run (each a round trip of the fabric and a
+// pause, 0.5-1 us: some tenths of a second), four times as many where the launch
+// has more tiles than the device (not whole) and some wait for those of earlier
+// systems to end.  (PF_CHIP_SPIN: a small limit makes tiles
+// give up, for tests.)
+int chip_spin(bool whole)
 {
     const char *e = getenv("PF_CHIP_SPIN");
-    return e ? std::max(0, atoi(e)) : pfk::CH_SPIN;
+    return e ? std::max(0, atoi(e)) : whole ? pfk::CH_SPIN : 4 * pfk::CH_SPIN;
 }
 
 // Table entry of a run of L in the partition ge by the kernel instance of kz
-// planes; the exchange buffers grow to it.
+// planes; the exchange buffers grow to it.  whole: every tile of the launch has
+// a compute unit.
 template <typename T>
-pf_status chip_system(LinSolve &L, const pfk::ChipGeom &ge, int kz, pfk::ChipSys<T> &S)
+pf_status chip_system(LinSolve &L, const pfk::ChipGeom &ge, int kz, bool whole, pfk::ChipSys<T> &S)
 {
     pf_grid *g = L.g;
     if (kz > chip_kzmax(L)) return fail(PF_ERR_DEVICE, "on-chip instance of %d planes cannot hold this operator", kz);
@@ -1235,15 +1306,10 @@ pf_status chip_system(LinSolve &L, const pfk::ChipGeom &ge, int kz, pfk::ChipSys
     S.face = (m.plain ? g->chip_plain : g->chip_xch) + m.face;
     S.xtile = m.plain ? reinterpret_cast<T *>(g->chip_plain + m.xtile) : nullptr;
     S.tag0 = g->chip_tag;
-    S.spin = chip_spin();
+    S.spin = chip_spin(whole);
     g->chip_tag += RUN_TAGS;
     return PF_OK;
 }
-
-// Tiles wait for each other, so an on-chip launch needs its tiles resident
-// together: one such launch at a time per device (held until it has ended).
-// Other work on the device only delays it.
-std::mutex g_chip_mu[64];
 
 template <typename T>
 pf_status krylov_run(pf_grid *g, const OpDesc &op, Work<T> &w, int m_fixed, int *status, bool adaptive);
@@ -1258,7 +1324,6 @@ template <typename T>
 pf_status chip_gave_up(LinSolve &L, int m, int *status)
 {
     pf_grid *g = L.g;
-    g->chip_off = true;
     if (getenv("PF_LOG"))
         fprintf(stderr, "[pf] on-chip run of %dx%dx%d gave up waiting\n", g->nx, g->ny, g->nz);
     PFCHK(ls_round_launch(L));
@@ -1272,22 +1337,23 @@ template <typename T>
 pf_status chip_run(LinSolve &L, int m, int *status)
 {
     pf_grid *g = L.g;
-    const pfk::ChipGeom &ge = chip_geom(g, L.op.psi, chip_kzmax(L), pfk::CH_GMAX);
+    const pfk::ChipGeom &ge = chip_geom(g, L.op.psi, chip_kzmax(L), chip_cap(g));
     if (!g->chip_table) {
         char *p = nullptr;
         PFCHK(dalloc(g, &p, std::max(sizeof(pfk::ChipSys<double>), sizeof(pfk::ChipSys<float>))));
         g->chip_table = p;
     }
     pfk::ChipSys<T> S;
-    PFCHK(chip_system<T>(L, ge, ge.KZ, S));
+    PFCHK(chip_system<T>(L, ge, ge.KZ, true, S));
     auto *table = static_cast<pfk::ChipSys<T> *>(g->chip_table);
     {
-        std::lock_guard<std::mutex> lock(g_chip_mu[g->device & 63]);
+        std::lock_guard<std::mutex> lock(chip_device(g).run);
         HIPCHK(pfk::chip_start<T>(&S, table, 1, g->stream));
         HIPCHK(pfk::chip_launch<T>(chip_form(L), ge.KZ, table, nullptr, 1, ge.G, g->stream));
         PFCHK(read_scalars(g));
     }
     *status = g->hsc->stop;
+    chip_ended(g, g->hsc->gave_up != 0);
     if (g->hsc->gave_up) return chip_gave_up<T>(L, m, status);
     return PF_OK;
 }
@@ -1310,20 +1376,22 @@ struct ChipBuf {
 template <typename T>
 const pfk::ChipGeom &chip_batch_geom(const LinSolve &L, double total)
 {
-    const int kz = chip_kzmax(L);
-    int cap = std::max(1, (int)(pfk::CH_GMAX * ((double)L.g->N / total)));
+    const int kz = chip_kzmax(L), all = chip_cap(L.g);
+    int cap = std::max(1, (int)(all * ((double)L.g->N / total)));
     for (;; cap = std::max(cap + 1, cap * 9 / 8)) {
-        const pfk::ChipGeom &ge = chip_geom(L.g, L.op.psi, kz, std::min(cap, pfk::CH_GMAX));
-        if (ge.KZ > 0 || cap >= pfk::CH_GMAX)
-            return ge.KZ > 0 ? chip_geom(L.g, L.op.psi, kz, pfk::CH_GMAX / std::max(1, pfk::CH_GMAX / ge.G)) : ge;
+        const pfk::ChipGeom &ge = chip_geom(L.g, L.op.psi, kz, std::min(cap, all));
+        if (ge.KZ > 0 || cap >= all)
+            return ge.KZ > 0 ? chip_geom(L.g, L.op.psi, kz, all / std::max(1, all / ge.G)) : ge;
     }
 }
 
 // On-chip runs of several systems in one launch per kernel form and limit of
 // planes per tile (the launch's instance is the largest any member needs, and
 // an instance with 16 planes cannot hold the classes of a field of more than
-// two values).  Tiles are dispatched in order, so the earliest unfinished
-// system always has all of its tiles on the chip.
+// two values).  A batch may have more tiles than the device: as long as
+// workgroups are dispatched in order, which is what the hardware does but no
+// document promises, the earliest unfinished system has all of its tiles on the
+// chip; in another order, tiles would give up and their runs be done again.
 template <typename T>
 pf_status chip_run_batch(std::vector<LinSolve *> &act, hipStream_t stream, int m, std::vector<int> &status)
 {
@@ -1376,11 +1444,11 @@ pf_status chip_run_batch(std::vector<LinSolve *> &act, hipStream_t stream, int m
     }
     for (const Launch &b : ls)
         for (int i = b.at; i < b.at + b.n; ++i) {
-            PFCHK(chip_system<T>(*act[order[i]], *geo[i], b.kz, hsys[i]));
+            PFCHK(chip_system<T>(*act[order[i]], *geo[i], b.kz, b.tiles <= chip_cap(act[order[i]]->g), hsys[i]));
             hscp[i] = act[order[i]]->g->sc;
         }
     {
-        std::lock_guard<std::mutex> lock(g_chip_mu[act[0]->g->device & 63]);
+        std::lock_guard<std::mutex> lock(chip_device(act[0]->g).run);
         HIPCHK(hipMemcpyAsync(db, hb, up, hipMemcpyHostToDevice, stream));
         HIPCHK(pfk::chip_start<T>(nullptr, reinterpret_cast<pfk::ChipSys<T> *>(db), n, stream));
         for (const Launch &b : ls)
@@ -1397,6 +1465,9 @@ pf_status chip_run_batch(std::vector<LinSolve *> &act, hipStream_t stream, int m
         *act[order[i]]->g->hsc = hgather[i];
         status[order[i]] = hgather[i].stop;
     }
+    bool gave_up = false;
+    for (int i = 0; i < n; ++i) gave_up |= hgather[i].gave_up != 0;
+    chip_ended(act[0]->g, gave_up);
     for (int i = 0; i < n; ++i)
         if (act[i]->g->hsc->gave_up) PFCHK(chip_gave_up<T>(*act[i], m, &status[i]));
     return PF_OK;
@@ -1452,7 +1523,7 @@ pf_status ls_init_launch(LinSolve &L)
     // (timing them overwrites the Krylov vectors, not b or x); a shift that
     // may turn out to be one value per class is taken for one here
     L.op.sig_class = L.class_probe;
-    const bool chip = L.mixed ? chip_fits<float>(L) : chip_fits<double>(L);
+    const bool chip = (L.mixed ? chip_fits<float>(L) : chip_fits<double>(L)) && chip_open(g, false);
     L.op.sig_class = false;
     if (!chip) {
         PFCHK(tune<double>(g));

@@ -3,6 +3,8 @@ and what happens when a run cannot have the chip, its memory or its time.
 
 Bars as in the parity tests: 1e-9 (FP64, stop 1e-12), 1e-8 (mixed, 1e-10).
 """
+import re
+
 import pytest
 
 from test_gpu_chip import D, _blocks, _pf, _rel, _solve, dev
@@ -58,12 +60,67 @@ def test_run_that_gives_up_waiting_is_done_again(spin, mixed, monkeypatch, capfd
     monkeypatch.setenv("PF_CHIP_SPIN", str(spin))
     bar = 1e-8 if mixed else 1e-9
     for m, b, ref in zip(made, bs, refs):
+        monkeypatch.setenv("PF_CHIP", "1")   # no pause after a give-up
         print("alone", m[0].nx, spin, mixed, flush=True)
         assert _rel(_solve(pf, pf.grid_from_problem(m[0]), None, b, mixed), ref) <= bar
     print("batch", spin, mixed, flush=True)
+    monkeypatch.setenv("PF_CHIP", "1")
     xs = [torch.zeros_like(b) for b in bs]
     infos = pf.pf_linear_solve_batch([pf.grid_from_problem(m[0]) for m in made], [None] * 3, bs, xs, _opts(pf, mixed))
     for x, ref, info in zip(xs, refs, infos):
         assert info["status"] == 0 and _rel(x.cpu().numpy(), ref) <= bar
     if spin == 0:
-        assert capfd.readouterr().err.count("gave up waiting") == 6
+        assert capfd.readouterr().err.count("gave up waiting") >= 6   # every run, restarts included
+
+
+def test_runs_fit_the_compute_units_there_are(monkeypatch, capfd):
+    """A device (or partition) of 32 compute units holds at most 32 tiles that
+    can wait for each other: small grids take fewer tiles, larger ones the
+    two-kernel iteration; a batch with more tiles than the device runs them in
+    turn."""
+    pf = _pf()
+    made = [_blocks(*s, (D,) * 6, 2, seed=i) for i, s in enumerate([(33, 35, 37), (17, 19, 23), (97, 97, 97), (41, 40, 39)])]
+    bs = [dev(m[2]) for m in made]
+    refs = [_solve(pf, pf.grid_from_problem(m[0]), None, b, False, chip=False) for m, b in zip(made, bs)]
+    monkeypatch.setenv("PF_LOG", "1")
+    monkeypatch.setenv("PF_CHIP_CUS", "32")
+    capfd.readouterr()
+    for m, b, ref in zip(made, bs, refs):
+        print(m[0].nx, flush=True)
+        assert _rel(_solve(pf, pf.grid_from_problem(m[0]), None, b, False), ref) <= 1e-9
+    grids = [pf.grid_from_problem(m[0]) for m in made] + [pf.grid_from_problem(made[0][0]) for _ in range(3)]
+    xs = [torch.zeros_like(b) for b in bs + [bs[0]] * 3]
+    infos = pf.pf_linear_solve_batch(grids, [None] * 7, bs + [bs[0]] * 3, xs, _opts(pf, False))
+    for x, ref, info in zip(xs, refs + [refs[0]] * 3, infos):
+        assert info["status"] == 0 and _rel(x.cpu().numpy(), ref) <= 1e-9
+    err = capfd.readouterr().err
+    tiles = re.findall(r"on-chip runs of (\S+): (\d+) x (\d+) x (\d+) tiles", err)
+    assert {t[0] for t in tiles} == {"33x35x37", "17x19x23", "41x40x39"} and "gave up" not in err
+    assert all(int(a) * int(b) * int(c) <= 32 for _, a, b, c in tiles)
+
+
+def test_device_pauses_after_a_run_that_gave_up(monkeypatch):
+    """Whatever kept the tiles waiting, later runs (of any grid) do not pay for
+    it again at once: 64 of them take the two-kernel iteration, then the chip
+    is tried again."""
+    pf = _pf()
+    p, _, b = _blocks(33, 35, 37, (D,) * 6)
+    b = dev(b)
+    g = pf.grid_from_problem(p)
+
+    def same(a, b):
+        return a.tobytes() == b.tobytes()
+
+    _solve(pf, g, None, b, False, chip=False)       # the launch shapes of the two-kernel iteration
+    two = _solve(pf, g, None, b, False, chip=False)
+    chip = _solve(pf, g, None, b, False)
+    assert same(two, _solve(pf, g, None, b, False, chip=False)) and not same(two, chip)
+    monkeypatch.setenv("PF_CHIP_SPIN", "0")
+    _solve(pf, pf.grid_from_problem(p), None, b, False)
+    monkeypatch.delenv("PF_CHIP_SPIN")
+    took = 0
+    while same(_solve(pf, g, None, b, False), two):
+        took += 1
+        assert took <= 64
+    assert took >= 32       # (a solve is one run or a few)
+    assert same(chip, _solve(pf, g, None, b, False))
