@@ -241,6 +241,16 @@ pf_status dalloc(pf_grid *g, T **p, size_t n)
     return PF_OK;
 }
 
+// Returns a buffer that no work on the device uses any more.
+template <typename T>
+void dfree(pf_grid *g, T **p)
+{
+    if (!*p) return;
+    g->allocs.erase(std::remove(g->allocs.begin(), g->allocs.end(), (void *)*p), g->allocs.end());
+    (void)hipFree(*p);
+    *p = nullptr;
+}
+
 template <typename T>
 pf_status fill(pf_grid *g, T *p, T v, size_t n)
 {
@@ -1271,12 +1281,19 @@ pf_status chip_system(LinSolve &L, const pfk::ChipGeom &ge, int kz, bool whole, 
     if (kz > chip_kzmax(L)) return fail(PF_ERR_DEVICE, "on-chip instance of %d planes cannot hold this operator", kz);
     Work<T> &w = work_of<T>(g);
     const pfk::ChipSpace m = pfk::chip_space(ge, kz, sizeof(T));
+    const char *most = getenv("PF_CHIP_MEM");   // bytes a grid may take (for tests)
+    if (most && m.tagged + m.plain > (size_t)atoll(most)) return fail(PF_ERR_ALLOC, "on-chip exchange memory refused");
+    // (grown buffers replace the old ones: every earlier run has ended)
     if (m.tagged > g->chip_xch_bytes) {
+        dfree(g, &g->chip_xch);
+        g->chip_xch_bytes = 0;
         PFCHK(dalloc(g, &g->chip_xch, m.tagged));
         g->chip_xch_bytes = m.tagged;
         g->chip_tag = 0;
     }
     if (m.plain > g->chip_plain_bytes) {
+        dfree(g, &g->chip_plain);
+        g->chip_plain_bytes = 0;
         PFCHK(dalloc(g, &g->chip_plain, m.plain));
         g->chip_plain_bytes = m.plain;
     }
@@ -1316,16 +1333,18 @@ pf_status krylov_run(pf_grid *g, const OpDesc &op, Work<T> &w, int m_fixed, int 
 
 pf_status ls_round_launch(LinSolve &L);
 
-// Tiles of an on-chip run gave up waiting: the two-kernel iteration from the
-// true residual of what is in x.  (An FP32 run solves for a correction, which
-// starts from zero again; in FP64 some tiles may have written their part of x,
+// A run meant for the chip by the two-kernel iteration after all (its memory
+// could not be had, or tiles gave up waiting), from the true residual of what
+// is in x.  (An FP32 run solves for a correction, which starts from zero again;
+// in FP64 some tiles of a run that gave up may have written their part of x,
 // any of which is a start as good as another.)
 template <typename T>
-pf_status chip_gave_up(LinSolve &L, int m, int *status)
+pf_status run_off_chip(LinSolve &L, int m, int *status, const char *why)
 {
     pf_grid *g = L.g;
-    if (getenv("PF_LOG"))
-        fprintf(stderr, "[pf] on-chip run of %dx%dx%d gave up waiting\n", g->nx, g->ny, g->nz);
+    if (getenv("PF_LOG")) fprintf(stderr, "[pf] on-chip run of %dx%dx%d %s\n", g->nx, g->ny, g->nz, why);
+    g_err.clear();
+    PFCHK(tune<T>(g));
     PFCHK(ls_round_launch(L));
     PFCHK(sync(g));
     L.rr = g->hsc->red[0];
@@ -1333,18 +1352,23 @@ pf_status chip_gave_up(LinSolve &L, int m, int *status)
     return krylov_run<T>(g, L.op, work_of<T>(g), m, status, L.o->check_every == 0);
 }
 
+constexpr const char *GAVE_UP = "gave up waiting", *NO_MEMORY = "has no exchange memory";
+
 template <typename T>
 pf_status chip_run(LinSolve &L, int m, int *status)
 {
     pf_grid *g = L.g;
     const pfk::ChipGeom &ge = chip_geom(g, L.op.psi, chip_kzmax(L), chip_cap(g));
+    pf_status st = PF_OK;
     if (!g->chip_table) {
         char *p = nullptr;
-        PFCHK(dalloc(g, &p, std::max(sizeof(pfk::ChipSys<double>), sizeof(pfk::ChipSys<float>))));
+        st = dalloc(g, &p, std::max(sizeof(pfk::ChipSys<double>), sizeof(pfk::ChipSys<float>)));
         g->chip_table = p;
     }
     pfk::ChipSys<T> S;
-    PFCHK(chip_system<T>(L, ge, ge.KZ, true, S));
+    if (st == PF_OK) st = chip_system<T>(L, ge, ge.KZ, true, S);
+    if (st == PF_ERR_ALLOC) return run_off_chip<T>(L, m, status, NO_MEMORY);
+    PFCHK(st);
     auto *table = static_cast<pfk::ChipSys<T> *>(g->chip_table);
     {
         std::lock_guard<std::mutex> lock(chip_device(g).run);
@@ -1354,7 +1378,7 @@ pf_status chip_run(LinSolve &L, int m, int *status)
     }
     *status = g->hsc->stop;
     chip_ended(g, g->hsc->gave_up != 0);
-    if (g->hsc->gave_up) return chip_gave_up<T>(L, m, status);
+    if (g->hsc->gave_up) return run_off_chip<T>(L, m, status, GAVE_UP);
     return PF_OK;
 }
 
@@ -1363,8 +1387,6 @@ pf_status chip_run(LinSolve &L, int m, int *status)
 struct ChipBuf {
     void *dev = nullptr, *host = nullptr;
     size_t bytes = 0;
-    Scalars *hsc = nullptr;
-    int hcap = 0;
 } g_chipb;
 
 // Partition of a batch member: within its share of the chip by unknowns, or
@@ -1395,27 +1417,30 @@ const pfk::ChipGeom &chip_batch_geom(const LinSolve &L, double total)
 template <typename T>
 pf_status chip_run_batch(std::vector<LinSolve *> &act, hipStream_t stream, int m, std::vector<int> &status)
 {
-    const int n = (int)act.size();
-    status.assign(n, pfk::ST_RUN);
-    std::vector<int> order(n);
-    for (int i = 0; i < n; ++i) order[i] = i;
+    const int all = (int)act.size();
+    status.assign(all, pfk::ST_RUN);
+    std::vector<int> order(all), off;   // off: members whose exchange memory could not be had
+    for (int i = 0; i < all; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
         const int fa = chip_form(*act[a]), fb = chip_form(*act[b]);
         const int ka = chip_kzmax(*act[a]), kb = chip_kzmax(*act[b]);
         return fa != fb ? fa < fb : ka != kb ? ka > kb : act[a]->g->N > act[b]->g->N;
     });
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    const size_t szT = al(sizeof(pfk::ChipSys<T>) * n), szF = al(sizeof(int) * (2 * n + 1)), szP = al(sizeof(void *) * n);
-    const size_t up = szT + szF + szP, need = up + al(sizeof(Scalars) * n);
+    const size_t szT = al(sizeof(pfk::ChipSys<T>) * all), szF = al(sizeof(int) * 2 * all), szP = al(sizeof(void *) * all);
+    const size_t up = szT + szF + szP, need = up + al(sizeof(Scalars) * all);
     if (need > g_chipb.bytes) {
         if (g_chipb.dev) (void)hipFree(g_chipb.dev);
         if (g_chipb.host) (void)hipHostFree(g_chipb.host);
         g_chipb.dev = g_chipb.host = nullptr;
         g_chipb.bytes = 0;
-        if (hipMalloc(&g_chipb.dev, need) != hipSuccess) return fail(PF_ERR_ALLOC, "batch table allocation failed");
-        if (hipHostMalloc(&g_chipb.host, need, hipHostMallocDefault) != hipSuccess)
-            return fail(PF_ERR_ALLOC, "batch pinned allocation failed");
-        g_chipb.bytes = need;
+        if (hipMalloc(&g_chipb.dev, need) == hipSuccess &&
+            hipHostMalloc(&g_chipb.host, need, hipHostMallocDefault) == hipSuccess) {
+            g_chipb.bytes = need;
+        } else {
+            (void)hipGetLastError();
+            off.swap(order);
+        }
     }
     char *hb = static_cast<char *>(g_chipb.host), *db = static_cast<char *>(g_chipb.dev);
     auto *hsys = reinterpret_cast<pfk::ChipSys<T> *>(hb);
@@ -1426,28 +1451,40 @@ pf_status chip_run_batch(std::vector<LinSolve *> &act, hipStream_t stream, int m
     for (const LinSolve *L : act) total += (double)L->g->N;
     struct Launch { int form, lim, kz, at, n, tiles, foff; };
     std::vector<Launch> ls;
-    std::vector<const pfk::ChipGeom *> geo(n);
-    int foff = 0;
-    for (int i = 0; i < n; ++i) {
-        geo[i] = &chip_batch_geom<T>(*act[order[i]], total);
-        const int form = chip_form(*act[order[i]]), lim = chip_kzmax(*act[order[i]]);
-        if (ls.empty() || ls.back().form != form || ls.back().lim != lim) {
-            if (!ls.empty()) ++foff;
-            ls.push_back(Launch{form, lim, 0, i, 0, 0, foff});
-            hfirst[foff] = 0;
+    for (bool again = !order.empty(); again;) {
+        again = false;
+        ls.clear();
+        std::vector<const pfk::ChipGeom *> geo;
+        int foff = 0;
+        for (int i = 0; i < (int)order.size(); ++i) {
+            geo.push_back(&chip_batch_geom<T>(*act[order[i]], total));
+            const int form = chip_form(*act[order[i]]), lim = chip_kzmax(*act[order[i]]);
+            if (ls.empty() || ls.back().form != form || ls.back().lim != lim) {
+                if (!ls.empty()) ++foff;
+                ls.push_back(Launch{form, lim, 0, i, 0, 0, foff});
+                hfirst[foff] = 0;
+            }
+            Launch &b = ls.back();
+            b.kz = std::max(b.kz, geo[i]->KZ);
+            b.n += 1;
+            b.tiles += geo[i]->G;
+            hfirst[++foff] = b.tiles;
         }
-        Launch &b = ls.back();
-        b.kz = std::max(b.kz, geo[i]->KZ);
-        b.n += 1;
-        b.tiles += geo[i]->G;
-        hfirst[++foff] = b.tiles;
+        for (const Launch &b : ls)
+            for (int i = b.at; i < b.at + b.n && !again; ++i) {
+                const pf_status st = chip_system<T>(*act[order[i]], *geo[i], b.kz, b.tiles <= chip_cap(act[order[i]]->g), hsys[i]);
+                if (st == PF_ERR_ALLOC) {   // the others without it
+                    off.push_back(order[i]);
+                    order.erase(order.begin() + i);
+                    again = !order.empty();
+                    break;
+                }
+                PFCHK(st);
+                hscp[i] = act[order[i]]->g->sc;
+            }
     }
-    for (const Launch &b : ls)
-        for (int i = b.at; i < b.at + b.n; ++i) {
-            PFCHK(chip_system<T>(*act[order[i]], *geo[i], b.kz, b.tiles <= chip_cap(act[order[i]]->g), hsys[i]));
-            hscp[i] = act[order[i]]->g->sc;
-        }
-    {
+    const int n = (int)order.size();
+    if (n > 0) {
         std::lock_guard<std::mutex> lock(chip_device(act[0]->g).run);
         HIPCHK(hipMemcpyAsync(db, hb, up, hipMemcpyHostToDevice, stream));
         HIPCHK(pfk::chip_start<T>(nullptr, reinterpret_cast<pfk::ChipSys<T> *>(db), n, stream));
@@ -1461,15 +1498,16 @@ pf_status chip_run_batch(std::vector<LinSolve *> &act, hipStream_t stream, int m
         HIPCHK(hipMemcpyAsync(hgather, db + up, sizeof(Scalars) * n, hipMemcpyDeviceToHost, stream));
         HIPCHK(hipStreamSynchronize(stream));
     }
+    bool gave_up = false;
     for (int i = 0; i < n; ++i) {
         *act[order[i]]->g->hsc = hgather[i];
         status[order[i]] = hgather[i].stop;
+        gave_up |= hgather[i].gave_up != 0;
     }
-    bool gave_up = false;
-    for (int i = 0; i < n; ++i) gave_up |= hgather[i].gave_up != 0;
-    chip_ended(act[0]->g, gave_up);
-    for (int i = 0; i < n; ++i)
-        if (act[i]->g->hsc->gave_up) PFCHK(chip_gave_up<T>(*act[i], m, &status[i]));
+    if (n > 0) chip_ended(act[0]->g, gave_up);
+    for (int i : order)
+        if (act[i]->g->hsc->gave_up) PFCHK(run_off_chip<T>(*act[i], m, &status[i], GAVE_UP));
+    for (int i : off) PFCHK(run_off_chip<T>(*act[i], m, &status[i], NO_MEMORY));
     return PF_OK;
 }
 

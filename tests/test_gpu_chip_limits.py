@@ -3,6 +3,7 @@ and what happens when a run cannot have the chip, its memory or its time.
 
 Bars as in the parity tests: 1e-9 (FP64, stop 1e-12), 1e-8 (mixed, 1e-10).
 """
+import os
 import re
 
 import pytest
@@ -124,3 +125,60 @@ def test_device_pauses_after_a_run_that_gave_up(monkeypatch):
         assert took <= 64
     assert took >= 32       # (a solve is one run or a few)
     assert same(chip, _solve(pf, g, None, b, False))
+
+
+@pytest.mark.parametrize("most", [0, 400_000])
+def test_runs_without_exchange_memory_take_the_two_kernel_iteration(most, monkeypatch, capfd):
+    """Where the exchange memory of a run cannot be had, the solve goes on
+    without it, alone and in a batch (whose other members stay on chip)."""
+    pf = _pf()
+    made = [_blocks(*s, (D,) * 6, 2, seed=20 + i) for i, s in enumerate([(65, 60, 63), (9, 9, 9), (113, 105, 113)])]
+    bs = [dev(m[2]) for m in made]
+    monkeypatch.setenv("PF_LOG", "1")
+    for mixed, bar in ((False, 1e-9), (True, 1e-8)):
+        refs = [_solve(pf, pf.grid_from_problem(m[0]), None, b, mixed, chip=False) for m, b in zip(made, bs)]
+        monkeypatch.setenv("PF_CHIP_MEM", str(most))
+        capfd.readouterr()
+        for m, b, ref in zip(made, bs, refs):
+            print("alone", m[0].nx, most, mixed, flush=True)
+            assert _rel(_solve(pf, pf.grid_from_problem(m[0]), None, b, mixed), ref) <= bar
+        print("batch", most, mixed, flush=True)
+        xs = [torch.zeros_like(b) for b in bs]
+        infos = pf.pf_linear_solve_batch([pf.grid_from_problem(m[0]) for m in made], [None] * 3, bs, xs, _opts(pf, mixed))
+        for x, ref, info in zip(xs, refs, infos):
+            assert info["status"] == 0 and _rel(x.cpu().numpy(), ref) <= bar
+        err = capfd.readouterr().err
+        assert "run of 113x105x113 has no exchange memory" in err and "run of 65x60x63 has no exchange memory" in err
+        assert ("run of 9x9x9 has no exchange memory" in err) == (most == 0)
+        monkeypatch.delenv("PF_CHIP_MEM")
+
+
+def test_grown_exchange_memory_replaces_the_old():
+    """FP64 runs take twice the exchange memory of FP32 runs (97^3: about 5 and
+    10 MB).  In whichever order a grid first needs them, it ends with the same
+    memory."""
+    pf = _pf()
+    p, _, b = _blocks(97, 97, 97, (D,) * 6)
+    b = dev(b)
+    x = torch.zeros_like(b)
+    opts = {m: pf.pf_lin_opts_default(rel_tol=1e-3, precision=pf.PF_MIXED if m else pf.PF_FP64) for m in (False, True)}
+
+    def used(order):
+        g = pf.grid_from_problem(p)
+        for m in (True, False):     # workspaces of both precisions, without the chip
+            os.environ["PF_CHIP"] = "0"
+            try:
+                pf.pf_linear_solve(g, None, b, x.zero_(), opts[m])
+            finally:
+                os.environ.pop("PF_CHIP")
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        for m in order:
+            pf.pf_linear_solve(g, None, b, x.zero_(), opts[m])
+        torch.cuda.synchronize()
+        return before - torch.cuda.mem_get_info()[0]
+
+    used((False, True))             # what the first use of the kernels themselves takes
+    large_first, small_first = used((False, True)), used((True, False))
+    print("exchange memory", large_first, small_first, flush=True)
+    assert 0 < large_first and small_first <= large_first + (2 << 20)
