@@ -19,6 +19,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -1180,9 +1181,16 @@ int chip_cap(pf_grid *g)
 // keep to the two-kernel iteration, four times as many after each further
 // time, up to 2^18; runs that end well take the steps back.  A give-up costs
 // about half a second, a run on chip saves about a millisecond.
+//
+// Launches of several threads share the compute units in the order they come:
+// used counts the tiles on the device, each launch's rounded up to the same
+// number on all eight XCDs (workgroups are dealt to them in turn), so that all
+// of them are resident.  Other work only delays them.
 struct ChipDevice {
-    std::mutex run;   // one on-chip launch at a time, held until it has ended (other work only delays it)
     std::mutex mu;
+    std::condition_variable cv;
+    unsigned long next = 0, turn = 0;
+    int used = 0;
     int strikes = 0;
     long pause = 0;
 } g_chip_dev[64];
@@ -1207,6 +1215,33 @@ bool chip_open(const pf_grid *g, bool take)
     if (take) --d.pause;
     return false;
 }
+
+// A launch's share of the device, until it has ended.
+class ChipShare {
+public:
+    ChipShare(pf_grid *g, int tiles) : d(chip_device(g)), n(std::min(chip_cap(g), (tiles + 7) / 8 * 8))
+    {
+        const int all = chip_cap(g);
+        std::unique_lock<std::mutex> lock(d.mu);
+        const unsigned long mine = d.next++;
+        d.cv.wait(lock, [&] { return d.turn == mine && (d.used == 0 || d.used + n <= all); });
+        d.used += n;
+        ++d.turn;
+        d.cv.notify_all();
+    }
+    ~ChipShare()
+    {
+        std::lock_guard<std::mutex> lock(d.mu);
+        d.used -= n;
+        d.cv.notify_all();
+    }
+    ChipShare(const ChipShare &) = delete;
+    ChipShare &operator=(const ChipShare &) = delete;
+
+private:
+    ChipDevice &d;
+    int n;
+};
 
 void chip_ended(const pf_grid *g, bool gave_up)
 {
@@ -1371,7 +1406,7 @@ pf_status chip_run(LinSolve &L, int m, int *status)
     PFCHK(st);
     auto *table = static_cast<pfk::ChipSys<T> *>(g->chip_table);
     {
-        std::lock_guard<std::mutex> lock(chip_device(g).run);
+        ChipShare share(g, ge.G);
         HIPCHK(pfk::chip_start<T>(&S, table, 1, g->stream));
         HIPCHK(pfk::chip_launch<T>(chip_form(L), ge.KZ, table, nullptr, 1, ge.G, g->stream));
         PFCHK(read_scalars(g));
@@ -1485,7 +1520,9 @@ pf_status chip_run_batch(std::vector<LinSolve *> &act, hipStream_t stream, int m
     }
     const int n = (int)order.size();
     if (n > 0) {
-        std::lock_guard<std::mutex> lock(chip_device(act[0]->g).run);
+        int tiles = 0;   // the launches follow each other on one stream
+        for (const Launch &b : ls) tiles = std::max(tiles, b.tiles);
+        ChipShare share(act[0]->g, tiles);
         HIPCHK(hipMemcpyAsync(db, hb, up, hipMemcpyHostToDevice, stream));
         HIPCHK(pfk::chip_start<T>(nullptr, reinterpret_cast<pfk::ChipSys<T> *>(db), n, stream));
         for (const Launch &b : ls)

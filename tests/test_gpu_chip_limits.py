@@ -5,6 +5,8 @@ Bars as in the parity tests: 1e-9 (FP64, stop 1e-12), 1e-8 (mixed, 1e-10).
 """
 import os
 import re
+import threading
+import time
 
 import pytest
 
@@ -182,3 +184,53 @@ def test_grown_exchange_memory_replaces_the_old():
     large_first, small_first = used((False, True)), used((True, False))
     print("exchange memory", large_first, small_first, flush=True)
     assert 0 < large_first and small_first <= large_first + (2 << 20)
+
+
+def test_threads_share_the_chip():
+    """Solves of several threads, each with its own grid: small runs side by
+    side (33x35x37 takes 90 of 256 tiles, so two fit), large ones in their turn,
+    every solution bit for bit the one of the solve by itself."""
+    pf = _pf()
+    shapes = [(33, 35, 37), (33, 35, 37), (17, 19, 23), (97, 97, 97), (41, 40, 39), (113, 105, 113)]
+    made = [_blocks(*s, (D,) * 6, 2, seed=i) for i, s in enumerate(shapes)]
+    grids = [pf.grid_from_problem(m[0]) for m in made]
+    bs = [dev(m[2]) for m in made]
+    refs = [_solve(pf, g, None, b, False) for g, b in zip(grids, bs)]
+    bad = []
+
+    def work(i):
+        x = torch.zeros_like(bs[i])
+        for _ in range(6):
+            x.zero_()
+            torch.cuda.current_stream().synchronize()
+            pf.pf_linear_solve(grids[i], None, bs[i], x, _opts(pf, False))
+            if x.cpu().numpy().tobytes() != refs[i].tobytes():
+                bad.append(shapes[i])
+
+    def run(jobs):
+        ts = [threading.Thread(target=f, args=a) for f, a in jobs]
+        t = time.perf_counter()
+        for th in ts:
+            th.start()
+        for th in ts:
+            th.join()
+        return time.perf_counter() - t
+
+    print("threads", flush=True)
+    run([(work, (i,)) for i in range(len(shapes))])
+    assert not bad
+
+    neg = [-b for b in bs[:2]]      # (no work on the default stream between the solves)
+
+    def many(i, x):
+        for _ in range(40):
+            pf.pf_linear_solve(grids[i], None, bs[i], x, _opts(pf, False, max_iter=100), check=False)
+            pf.pf_linear_solve(grids[i], None, neg[i], x, _opts(pf, False, max_iter=100), check=False)
+
+    x0, x1 = torch.zeros_like(bs[0]), torch.zeros_like(bs[1])
+    ratio = []
+    for _ in range(3):
+        one = run([(many, (0, x0))]) + run([(many, (1, x1))])
+        ratio.append(run([(many, (0, x0)), (many, (1, x1))]) / one)
+    print("two threads / one after the other", ratio, flush=True)
+    assert sorted(ratio)[1] <= 0.75       # 0.5 where they overlap in full, about 0.9 in turn
