@@ -1576,6 +1576,20 @@ pf_status ls_init_launch(LinSolve &L)
     PFCHK(ensure_work<double>(g));
     L.mixed = L.o->precision == PF_MIXED;
     if (L.mixed) PFCHK(ensure_work<float>(g));
+    // (not for the outer loop's own shift, the Fermi derivative, which
+    // varies over the solvent)
+    L.class_probe = L.op.sigma && L.op.sigma != g->sig && !L.op.psi && use_palette(g) && shift_class_enabled();
+    // launch shapes of the two-kernel iteration, where its runs will use them,
+    // before anything of this solve is on the device but b and x (timing the
+    // shapes overwrites the Krylov vectors and the scalar block); a shift that
+    // may turn out to be one value per class is taken for one here
+    L.op.sig_class = L.class_probe;
+    const bool chip = (L.mixed ? chip_fits<float>(L) : chip_fits<double>(L)) && chip_open(g, false);
+    L.op.sig_class = false;
+    if (!chip) {
+        PFCHK(tune<double>(g));
+        if (L.mixed) PFCHK(tune<float>(g));
+    }
     if (L.op.sigma) {   // sigma >= 0 on free rows, read back with ||b_lift||
         PFCHK(fill<int>(g, &g->sc->neg_shift, 0, 1));
         hipLaunchKernelGGL(pfk::k_check_shift, dim3(pw_blocks(g->N)), dim3(NT), 0, g->stream, g->N, L.op.sigma,
@@ -1590,20 +1604,6 @@ pf_status ls_init_launch(LinSolve &L)
         L.op.sigma = g->sig64;
     }
     if (L.mixed) PFCHK(prepare_f32(g, L.op));
-    L.op.sig_class = false;
-    // (not for the outer loop's own shift, the Fermi derivative, which
-    // varies over the solvent)
-    L.class_probe = L.op.sigma && L.op.sigma != g->sig && !L.op.psi && use_palette(g) && shift_class_enabled();
-    // launch shapes of the two-kernel iteration, where its runs will use them
-    // (timing them overwrites the Krylov vectors, not b or x); a shift that
-    // may turn out to be one value per class is taken for one here
-    L.op.sig_class = L.class_probe;
-    const bool chip = (L.mixed ? chip_fits<float>(L) : chip_fits<double>(L)) && chip_open(g, false);
-    L.op.sig_class = false;
-    if (!chip) {
-        PFCHK(tune<double>(g));
-        if (L.mixed) PFCHK(tune<float>(g));
-    }
     if (L.class_probe) {   // is sigma one value per palette class?  read back with ||b_lift||
         if (!g->smm) {
             PFCHK(dalloc(g, &g->smm, 2 * pfk::PAL_MAX));
