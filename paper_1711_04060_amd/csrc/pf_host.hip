@@ -1108,6 +1108,7 @@ struct LinSolve {
     bool class_probe = false;   // the shift-per-class test ran in the set-up
     bool chip = false;          // the coming Krylov run is an on-chip one
     double run_tol2 = 0;        // its tolerance
+    bool cut = false;           // the last run ended at the iterations of one launch
     pf_status result = PF_OK;
 };
 
@@ -1135,9 +1136,16 @@ int chip_kzmax(const LinSolve &L)
     return (L.g->npal > 2 || chip_form(L) == pfk::CHF_NODE) ? 8 : 16;
 }
 
-// Iterations of one launch (a run that reaches them returns to the true
-// residual and starts again).
+// Iterations of one launch, about a second at most, so that other work on the
+// device is not kept waiting for longer.  A run that reaches them goes on from
+// the true residual; that counts neither as a restart or refinement nor towards
+// a stall.  (PF_CHIP_RUN: fewer, for tests.)
 constexpr int CHIP_MAX_RUN = 1 << 16;
+int chip_run_len()
+{
+    const char *e = getenv("PF_CHIP_RUN");
+    return e ? std::min(CHIP_MAX_RUN, std::max(1, atoi(e))) : CHIP_MAX_RUN;
+}
 
 const pfk::ChipGeom &chip_geom(pf_grid *g, bool psi, int kzmax, int gcap)
 {
@@ -1291,7 +1299,7 @@ pf_status ls_start(LinSolve &L, double tol2, bool zero_x)
         }
         return krylov_start<T>(g, work_of<T>(g), L.rr, tol2, L.iter, L.o->max_iter, zero_x);
     }
-    *L.g->hsc = krylov_init(L.rr, tol2, L.iter, std::min(L.o->max_iter, L.iter + CHIP_MAX_RUN));
+    *L.g->hsc = krylov_init(L.rr, tol2, L.iter, (int)std::min<long>(L.o->max_iter, (long)L.iter + chip_run_len()));
     return PF_OK;
 }
 
@@ -1709,12 +1717,12 @@ pf_status ls_round_decide(LinSolve &L, bool *run)
         // a tolerance below the attainable accuracy (rounding of A x at the
         // operator's condition number) shows as runs that end by the
         // recurrence while the true residual stays put: stop after three
-        if (L.started) {
+        if (L.started && !L.cut) {
             L.stall = (L.rr > 0.25 * L.rr_best) ? L.stall + 1 : 0;
             if (L.stall >= 3) { L.result = PF_ERR_NOCONV; L.done = true; return PF_OK; }
         }
         L.rr_best = std::min(L.rr_best, L.rr);
-        if (L.started) ++L.restarts;
+        if (L.started && !L.cut) ++L.restarts;
         if (L.restarts > 1000) { L.result = PF_ERR_BREAKDOWN; L.done = true; return PF_OK; }
         L.started = true;
         PFCHK(ls_start<double>(L, L.tol2, false));
@@ -1724,7 +1732,7 @@ pf_status ls_round_decide(LinSolve &L, bool *run)
             L.done = true;
             return PF_OK;
         }
-        ++L.refinements;
+        if (!L.cut) ++L.refinements;
         L.rr_start = L.rr;
         const double itol2 = L.o->inner_tol * L.o->inner_tol;
         PFCHK(ls_start<float>(L, std::max(itol2 * L.rr, L.tol2), true));
@@ -1740,6 +1748,7 @@ pf_status ls_after(LinSolve &L, int st, bool gpu = true)
 {
     pf_grid *g = L.g;
     L.iter = g->hsc->iter_done;
+    L.cut = L.chip && st == pfk::ST_MAXIT && L.iter < L.o->max_iter;
     if (L.mixed) {
         // keep x from before the correction; a non-finite FP32 run adds
         // nothing, so the next true residual equals the last one and the

@@ -234,3 +234,32 @@ def test_threads_share_the_chip():
         ratio.append(run([(many, (0, x0)), (many, (1, x1))]) / one)
     print("two threads / one after the other", ratio, flush=True)
     assert sorted(ratio)[1] <= 0.75       # 0.5 where they overlap in full, about 0.9 in turn
+
+
+@pytest.mark.parametrize("mixed", [False, True])
+def test_run_cut_at_the_iterations_of_a_launch_goes_on(mixed, monkeypatch):
+    """A launch ends after a number of iterations.  The solve goes on from the
+    true residual as often as it takes, to the caller's limit of iterations:
+    not counted as restarts, refinements or stalled runs, of which a few end a
+    solve."""
+    pf = _pf()
+    p, _, b = _blocks(33, 35, 37, (D,) * 6)
+    b = dev(b)
+    ref = _solve(pf, pf.grid_from_problem(p), None, b, mixed, chip=False)
+    monkeypatch.setenv("PF_CHIP_RUN", "24")
+    g = pf.grid_from_problem(p)
+    for batch in (False, True):
+        x = torch.zeros_like(b)
+        opts = _opts(pf, mixed, max_iter=20000)
+        print("batch", batch, mixed, flush=True)
+        if batch:
+            info = pf.pf_linear_solve_batch([g], [None], [b], [x], opts)[0]
+        else:
+            info = pf.pf_linear_solve(g, None, b, x, opts)
+        assert info["status"] == 0 and info["restarts"] <= 2 and info["refinements"] <= 6 and not info["fp64_fallback"]
+        assert _rel(x.cpu().numpy(), ref) <= (1e-8 if mixed else 1e-9)
+    # a few iterations a launch make next to no progress: the limit ends it, nothing else
+    monkeypatch.setenv("PF_CHIP_RUN", "2")
+    with pytest.raises(pf.PfError) as e:
+        pf.pf_linear_solve(g, None, b, torch.zeros_like(b), _opts(pf, False, max_iter=60))
+    assert e.value.code == pf.PF_ERR_NOCONV and "after 60 iterations" in str(e.value)
