@@ -1176,7 +1176,9 @@ struct SpeciesDev {
 // ends with the step after which the remaining error is below the rounding of
 // S: L' is at least min p, and L'' and L''' are the variance and the third
 // cumulant of values in [min p, max p], which bounds the error by c2 d^2 or
-// c3 |d|^3 (species_dev).  Bound by the exponentials, nsp + 1 a step.
+// c3 |d|^3 (species_dev); or with a step d at the rounding of S itself, which
+// those bounds need not allow where a species is much smaller than the others
+// (radii 1e-5 : 1, min p 1e-15).  Bound by the exponentials, nsp + 1 a step.
 // Everything stays in the log domain: |z_i phi| reaches 10^3 at charged nodes.
 // NS: the number of species where it is known to the compiler (the
 // exponentials of a step then overlap), 0: read from sp.
@@ -1205,7 +1207,8 @@ __device__ __forceinline__ double steric_root(double phi, const SpeciesDev &sp)
         // Newton L / L', Halley 2 L L' / (2 L'^2 - L L'')
         const double step = L * sum * (near ? 2.0 * dsum / (2.0 * d2 - lv) : 1.0 / dsum), d = fabs(step);
         S -= step;
-        if (!((near ? sp.c3 * d : sp.c2) * (d * d) > 1.1102230246251565e-16 * fmax(1.0, fabs(S)))) return S;
+        const double u = 1.1102230246251565e-16 * fmax(1.0, fabs(S));
+        if (!((near ? sp.c3 * d : sp.c2) * (d * d) > u) || d <= 8.0 * u) return S;
     }
     return S;
 }
