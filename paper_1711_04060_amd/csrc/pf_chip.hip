@@ -219,7 +219,10 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
     T *const st = ft + FTAB;
     T *const PX = st + PAL_MAX;              // BIG: p^ of the own nodes
     __shared__ double stot[4][CH_NQ], bred[NW][CH_NQ];
-    __shared__ int sfail;
+    // (what only a failed poll needs is kept here: in registers it cost 2-4% of
+    // an iteration)
+    __shared__ int sfail, slimit;
+    __shared__ __attribute__((address_space(1))) int *sgave;
     __shared__ unsigned snear;
 
     int si = 0, lb = blockIdx.x;
@@ -233,7 +236,6 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
         lb -= first[si];
     }
     const ChipSys<T> &S = table[si];
-    const int spin_max = S.spin;
     const int nx = S.nx, ny = S.ny, nz = S.nz, P = S.P, G = S.ge.G;
     lb = xcd_remap(lb, G);   // an XCD's tiles lie together
     const int cx = S.ge.c[0], cy = S.ge.c[1], cz = S.ge.c[2];
@@ -293,7 +295,11 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
         pub[u] = k < nk ? k * LP + q : DUMMY;
     }
 
-    if (tid == 0) sfail = 0;
+    if (tid == 0) {
+        sfail = 0;
+        slimit = S.spin;
+        sgave = (__attribute__((address_space(1))) int *)&S.sc->gave_up;
+    }
     for (int e = tid; e < KZ * LP; e += NT) L[e] = T(0);
     if constexpr (PAL) {
         if (tid < FTAB) ft[tid] = S.ftab[tid];
@@ -539,6 +545,10 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
     // L2 only (nearby tiles are, where the dispatcher deals the workgroups to
     // the XCDs in turn; the ids are the hardware's own)
     const unsigned xcc = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 15u;   // HW_REG_XCC_ID
+    auto give_up = [&]() {
+        sfail = 1;
+        __hip_atomic_store(sgave, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     unsigned near = 0;
     if (tid < 64) {
         if (tid == 0) __builtin_amdgcn_raw_buffer_store_b64(u32x2{xcc, tag0}, xi, (unsigned)lb * 8u, 0, SC1);
@@ -552,8 +562,8 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
         for (int spin = 0;; ++spin) {
             w = __builtin_amdgcn_raw_buffer_load_b64(xi, (unsigned)(lb + d) * 8u, 0, SC1);
             if (!__any(w.y != tag0)) break;
-            if (spin >= spin_max) {
-                sfail = 1;
+            if (spin >= slimit) {
+                give_up();
                 break;
             }
             __builtin_amdgcn_s_sleep(CH_SLEEP);
@@ -564,13 +574,7 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
         if (tid == 0) snear = near;
     }
     __syncthreads();
-    auto give_up = [&]() {
-        if (tid == 0) __hip_atomic_store(&S.sc->gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    if (sfail) {
-        give_up();
-        return;
-    }
+    if (sfail) return;
     near = snear;
     unsigned local = 0;   // bit u: slot u's reader is near
 #pragma unroll
@@ -644,8 +648,8 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
         if (two && tid < 64 && lb == gat) {
             for (int spin = 0;; ++spin) {
                 if (!__any(group_sums())) break;
-                if (spin >= spin_max) {
-                    sfail = 1;
+                if (spin >= slimit) {
+                    give_up();
                     break;
                 }
                 asm volatile("" ::: "memory");   // every poll reads again
@@ -689,8 +693,8 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
                 z[1] = zhi_in ? xval(zw[1]) : T(0);
             }
             if (!__any(miss)) break;
-            if (spin >= spin_max) {
-                sfail = 1;
+            if (spin >= slimit) {
+                give_up();
                 break;
             }
             __builtin_amdgcn_s_sleep(BIG ? CH_SLEEPB : CH_SLEEP);
@@ -767,10 +771,7 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
             T ht[HS], zt[2] = {T(0), T(0)};
 #pragma unroll
             for (int u = 0; u < HS; ++u) ht[u] = T(0);
-            if (!receive(ph - 1, ht, zt, tot)) {
-                give_up();
-                return;
-            }
+            if (!receive(ph - 1, ht, zt, tot)) return;
             const FinB f = fin_b(&sc, tot, 0);
             if (f.update) {
                 iter = f.iter;
@@ -853,10 +854,7 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
         ++ph;
         // ---- step B: s^ = r^ - alpha v^, t^ = D^-1 A s^
         double tot2[2];
-        if (!receive(ph - 1, hv, zv, tot2)) {
-            give_up();
-            return;
-        }
+        if (!receive(ph - 1, hv, zv, tot2)) return;
         rr = tot2[1];
         double alpha = 0.0;
         if (!finite(tot2[0]) || !finite(rr)) stop = ST_NONFINITE;
