@@ -188,10 +188,12 @@ struct pf_grid {
     double *dval = nullptr;
     double *q = nullptr;               // fixed charge (may stay null)
 
-    ZCfg c64, c32;     // step A of BiCGSTAB, residual and plain products
+    ZCfg c64, c32;     // step A of BiCGSTAB, and the residual of its solves
     ZCfg cb64, cb32;   // step B of BiCGSTAB (tuned on its own: lighter kernel)
     ZCfg cp64, cp32;   // standalone Jacobi-scaled product (tuned on first use)
-    bool tunedp64 = false, tunedp32 = false;
+    ZCfg cr64;         // standalone residual and plain product (tuned on first use)
+    ZCfg cd64;         // untuned: the residuals of on-chip solves
+    bool tunedp64 = false, tunedp32 = false, tunedr = false;
     int Gmax = 1;
 
     // linear solver state
@@ -890,23 +892,27 @@ pf_status tune(pf_grid *g)
     return PF_OK;
 }
 
-// Shapes of the standalone Jacobi-scaled product, per (grid shape, precision).
-std::map<std::tuple<int, int, int, int>, ZCfg> g_tuned_p;
+// Shapes of the kernels that also run on their own, per (grid shape,
+// precision): the Jacobi-scaled product, and the residual (also used by the
+// plain product).
+using ShapeMap = std::map<std::tuple<int, int, int, int>, ZCfg>;
+ShapeMap g_tuned_p, g_tuned_r;
 
-// Time the Jacobi-scaled product D^-1 A x over the candidate shapes on this
-// grid and keep the fastest.  Its three streams (x, eps in; y out) favour
-// other shapes than the eleven of step A.  Timed launches cycle through four
-// (x, y) pairs of the grid's workspace so that consecutive launches do not
-// find their vectors in the Infinity Cache.
-template <typename T>
-pf_status tune_product(pf_grid *g, const OpDesc &op)
+// Time kernel OP (the Jacobi-scaled product D^-1 A x or the residual b - A x)
+// over the candidate shapes on this grid and keep the fastest.  Their three or
+// four streams favour other shapes than the eleven of step A (residual at
+// 113^3, of a whole call: 58 us in step A's shape, 47 in the untuned one; at
+// 129^3 67 and 83).  Timed launches cycle through four (x, y) pairs of the grid's
+// workspace so that consecutive launches do not find their vectors in the
+// Infinity Cache.
+template <int OP, typename T>
+pf_status tune_alone(pf_grid *g, const OpDesc &op, ZCfg &cfg, bool &done, ShapeMap &kept)
 {
-    bool &done = sizeof(T) == 8 ? g->tunedp64 : g->tunedp32;
     if (done || !tuning_enabled()) return PF_OK;
     const auto key = std::make_tuple(g->nx, g->ny, g->nz, (int)sizeof(T));
-    auto found = g_tuned_p.find(key);
-    if (found != g_tuned_p.end()) {
-        cfgp_ref<T>(g) = found->second;
+    auto found = kept.find(key);
+    if (found != kept.end()) {
+        cfg = found->second;
         done = true;
         return PF_OK;
     }
@@ -921,13 +927,18 @@ pf_status tune_product(pf_grid *g, const OpDesc &op)
     HIPCHK(hipEventCreate(&e0));
     HIPCHK(hipEventCreate(&e1));
     pf_status st = PF_OK;
-    ZCfg best = cfgp_ref<T>(g);
+    ZCfg best = cfg;
     float best_ms = 1e30f;
     for (const ZCfg &c : tune_candidates<T>(g)) {
+        if (OP == pfk::OP_RESID && c.depth != 1) continue;   // comes in one pipeline depth
         pfk::ZArgs<T> a = zbase_cfg<T>(g, op, c);
-        a.x = xs[0];
-        a.out = ys[0];
-        if (zlaunch<pfk::OP_SPMV_JAC, T>(g, op, a, c) != PF_OK) {   // shape not launchable here
+        auto launch = [&](int k) {
+            a.x = xs[k & 3];
+            a.out = ys[k & 3];
+            if constexpr (OP == pfk::OP_RESID) a.b = xs[(k + 1) & 3];
+            return zlaunch<OP, T>(g, op, a, c);
+        };
+        if (launch(0) != PF_OK) {   // shape not launchable here
             (void)hipGetLastError();
             g_err.clear();
             continue;
@@ -936,11 +947,7 @@ pf_status tune_product(pf_grid *g, const OpDesc &op)
         float ms_c = 1e30f;
         for (int run = 0; run < 2 && st == PF_OK; ++run) {
             if (hipEventRecord(e0, g->stream) != hipSuccess) { st = fail(PF_ERR_DEVICE, "event record failed"); break; }
-            for (int k = 0; k < K && st == PF_OK; ++k) {
-                a.x = xs[k & 3];
-                a.out = ys[k & 3];
-                st = zlaunch<pfk::OP_SPMV_JAC, T>(g, op, a, c);
-            }
+            for (int k = 0; k < K && st == PF_OK; ++k) st = launch(k);
             if (st != PF_OK) break;
             if (hipEventRecord(e1, g->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
                 st = fail(PF_ERR_DEVICE, "event timing failed");
@@ -956,14 +963,25 @@ pf_status tune_product(pf_grid *g, const OpDesc &op)
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (st != PF_OK) return st;
-    cfgp_ref<T>(g) = best;
-    g_tuned_p[key] = best;
+    cfg = best;
+    kept[key] = best;
     done = true;
     if (getenv("PF_LOG"))
-        fprintf(stderr, "[pf] tuned %dx%dx%d %s product: threads %d strip %d z-planes %d depth %d (%.1f us)\n",
-                g->nx, g->ny, g->nz, sizeof(T) == 8 ? "fp64" : "fp32", best.NTZ, best.S, best.KZ, best.depth,
-                best_ms * 1e3);
+        fprintf(stderr, "[pf] tuned %dx%dx%d %s %s: threads %d strip %d z-planes %d depth %d (%.1f us)\n",
+                g->nx, g->ny, g->nz, sizeof(T) == 8 ? "fp64" : "fp32", OP == pfk::OP_RESID ? "residual" : "product",
+                best.NTZ, best.S, best.KZ, best.depth, best_ms * 1e3);
     return PF_OK;
+}
+
+template <typename T>
+pf_status tune_product(pf_grid *g, const OpDesc &op)
+{
+    return tune_alone<pfk::OP_SPMV_JAC, T>(g, op, cfgp_ref<T>(g), sizeof(T) == 8 ? g->tunedp64 : g->tunedp32, g_tuned_p);
+}
+
+pf_status tune_residual(pf_grid *g)
+{
+    return tune_alone<pfk::OP_RESID, double>(g, OpDesc{}, g->cr64, g->tunedr, g_tuned_r);
 }
 
 int chunk_len(const pf_grid *g, const pf_lin_opts *o)
@@ -1108,6 +1126,7 @@ struct LinSolve {
     bool class_probe = false;   // the shift-per-class test ran in the set-up
     bool chip = false;          // the coming Krylov run is an on-chip one
     double run_tol2 = 0;        // its tolerance
+    const ZCfg *rcfg = nullptr; // launch shape of its residuals (null: the one of step A)
     bool cut = false;           // the last run ended at the iterations of one launch
     pf_status result = PF_OK;
 };
@@ -1280,7 +1299,7 @@ bool chip_fits(const LinSolve &L)
     return chip_geom(g, L.op.psi, chip_kzmax(L), chip_cap(g)).KZ > 0;
 }
 
-pf_status ls_round_residual(LinSolve &L);
+pf_status ls_round_launch(LinSolve &L);
 
 // Start of the next Krylov run: nothing to do yet for an on-chip run.
 template <typename T>
@@ -1289,13 +1308,16 @@ pf_status ls_start(LinSolve &L, double tol2, bool zero_x)
     L.run_tol2 = tol2;
     L.chip = chip_fits<T>(L) && chip_open(L.g, true);
     if (!L.chip) {
-        // an on-chip run was expected (set-up), or an FP32 run before this
-        // FP64 one: the start is computed again after the shapes were timed
+        // an on-chip run was expected (set-up): the start is computed again,
+        // in the shapes of the two-kernel iteration
         pf_grid *g = L.g;
-        if (tuning_enabled() && !(sizeof(T) == 8 ? g->tuned : g->tuned32)) {
-            PFCHK(tune<T>(g));
-            PFCHK(ls_round_residual(L));
+        if (L.rcfg) {
+            L.rcfg = nullptr;
+            PFCHK(tune<double>(g));
+            if (sizeof(T) == 4) PFCHK(tune<T>(g));
+            PFCHK(ls_round_launch(L));
             PFCHK(sync(g));
+            L.rr = g->hsc->red[0];
         }
         return krylov_start<T>(g, work_of<T>(g), L.rr, tol2, L.iter, L.o->max_iter, zero_x);
     }
@@ -1373,8 +1395,6 @@ pf_status chip_system(LinSolve &L, const pfk::ChipGeom &ge, int kz, bool whole, 
 
 template <typename T>
 pf_status krylov_run(pf_grid *g, const OpDesc &op, Work<T> &w, int m_fixed, int *status, bool adaptive);
-
-pf_status ls_round_launch(LinSolve &L);
 
 // A run meant for the chip by the two-kernel iteration after all (its memory
 // could not be had, or tiles gave up waiting), from the true residual of what
@@ -1562,9 +1582,9 @@ pf_status ls_round_residual(LinSolve &L)
 {
     pf_grid *g = L.g;
     if (L.mixed)
-        PFCHK(residual64(g, L.op, g->b64, g->w64.x, g->w64.r, false, g->w32.rt, nullptr, g->w32.s));
+        PFCHK(residual64(g, L.op, g->b64, g->w64.x, g->w64.r, false, g->w32.rt, nullptr, g->w32.s, 0, L.rcfg));
     else
-        PFCHK(residual64(g, L.op, g->b64, g->w64.x, g->w64.r, false, g->w64.rt, g->w64.s, nullptr));
+        PFCHK(residual64(g, L.op, g->b64, g->w64.x, g->w64.r, false, g->w64.rt, g->w64.s, nullptr, 0, L.rcfg));
     if (L.o->stop_rule == PF_STOP_ABS_INF) {   // ||r||_inf of the free rows into red[2]
         const int B = pw_blocks(g->N);
         hipLaunchKernelGGL(pfk::k_maxabs_free<NT>, dim3(B), dim3(NT), 0, g->stream, g->N, (const double *)g->w64.r,
@@ -1594,6 +1614,11 @@ pf_status ls_init_launch(LinSolve &L)
     L.op.sig_class = L.class_probe;
     const bool chip = (L.mixed ? chip_fits<float>(L) : chip_fits<double>(L)) && chip_open(g, false);
     L.op.sig_class = false;
+    // (an on-chip solve keeps to the untuned residual, whatever else has been
+    // timed on the grid meanwhile: a solve equals the same solve before it.
+    // Timing steps A and B takes 65-117 ms at 33^3-129^3, and the residual gains
+    // 3-16 us of it)
+    L.rcfg = chip ? &g->cd64 : nullptr;
     if (!chip) {
         PFCHK(tune<double>(g));
         if (L.mixed) PFCHK(tune<float>(g));
@@ -1630,7 +1655,7 @@ pf_status ls_init_launch(LinSolve &L)
     hipLaunchKernelGGL(pfk::k_set_dirichlet, dim3(pw_blocks(g->N)), dim3(NT), 0, g->stream, g->N, g->w64.x,
                        (const uint8_t *)g->flags, dirbit(L.op), L.op.psi ? nullptr : (const double *)g->dval);
     HIPCHK(hipGetLastError());
-    PFCHK(residual64(g, L.op, g->b64, nullptr, g->w64.r, true, nullptr, nullptr, nullptr, 1));
+    PFCHK(residual64(g, L.op, g->b64, nullptr, g->w64.r, true, nullptr, nullptr, nullptr, 1, L.rcfg));
     PFCHK(ls_round_residual(L));
     HIPCHK(hipMemcpyAsync(g->hsc, g->sc, sizeof(Scalars), hipMemcpyDeviceToHost, g->stream));
     return PF_OK;
@@ -2703,7 +2728,7 @@ pf_status pf_grid_create(const pf_grid_desc *d, pf_grid **out)
     for (int f = 0; f < 6; ++f) g->bcval[f] = d->bc_value[f];
     g->ustream = (hipStream_t)d->stream;
     g->pinned_shape = g_nt_override || g_ppt_override || g_kz_override || g_depth_override;
-    g->c64 = g->cb64 = g->cp64 = default_cfg(d->nx, d->ny, d->nz, 8);
+    g->c64 = g->cb64 = g->cp64 = g->cr64 = g->cd64 = default_cfg(d->nx, d->ny, d->nz, 8);
     g->c32 = g->cb32 = g->cp32 = default_cfg(d->nx, d->ny, d->nz, 4);
     if (g->c64.lds > LDS_MAX || g->c32.lds > LDS_MAX) {
         delete g;
@@ -2811,11 +2836,12 @@ pf_status pf_residual(pf_grid *g, const double *sigma, const double *b, const do
     if (!b || !x || !rel_res) return fail(PF_ERR_ARG, "b, x and rel_res are required");
     PFCHK(begin(g));
     PFCHK(ensure_work<double>(g));
+    PFCHK(tune_residual(g));
     OpDesc op;
     op.sigma = sigma;
     double *rbuf = r ? r : g->w64.r;
-    PFCHK(residual64(g, op, b, nullptr, rbuf, true, nullptr, nullptr, nullptr, 1));
-    PFCHK(residual64(g, op, b, x, rbuf, false, nullptr, nullptr, nullptr, 0));
+    PFCHK(residual64(g, op, b, nullptr, rbuf, true, nullptr, nullptr, nullptr, 1, &g->cr64));
+    PFCHK(residual64(g, op, b, x, rbuf, false, nullptr, nullptr, nullptr, 0, &g->cr64));
     PFCHK(read_scalars(g));
     const double bn2 = g->hsc->red[1];
     const double rr = g->hsc->red[0];
@@ -2875,7 +2901,7 @@ pf_status pf_residual_noalloc(pf_grid *g, const double *sigma, const double *b, 
     const size_t head = (sizeof(Scalars) + 255) & ~(size_t)255;
     const size_t cap = (PF_NOALLOC_SCRATCH_BYTES - head) / (pfk::PSTRIDE * sizeof(double));
     // pf_residual's launch shape; longer z-chunks only if its partials do not fit
-    ZCfg c = cfg_of<double>(g);
+    ZCfg c = g->cr64;
     while ((size_t)c.G > cap && c.KZ < g->nz) c = make_cfg(g->nx, g->ny, g->nz, 8, c.NTZ, c.PPT, 2 * c.KZ, 1);
     if ((size_t)c.G > cap)
         return fail(PF_ERR_ARG, "grid needs %d workgroup partials; the scratch holds %zu", c.G, cap);
@@ -2950,8 +2976,8 @@ pf_status pf_spmv(pf_grid *g, const double *sigma, const double *x, double *y, i
     PFCHK(ensure_work<double>(g));
     OpDesc op;
     op.sigma = sigma;
-    if (jacobi) PFCHK(tune_product<double>(g, op));
-    const ZCfg &c = jacobi ? cfgp_ref<double>(g) : cfg_of<double>(g);
+    PFCHK(jacobi ? tune_product<double>(g, op) : tune_residual(g));
+    const ZCfg &c = jacobi ? g->cp64 : g->cr64;
     pfk::ZArgs<double> a = zbase_cfg<double>(g, op, c);
     a.x = x;
     a.out = y;

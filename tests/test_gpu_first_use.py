@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import oracle
-from test_gpu_chip import D, _blocks, _pf, _rel, dev
+from test_gpu_chip import D, _blocks, _pf, _rel, _solve, dev
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -44,3 +44,33 @@ def test_negative_shift_is_refused_on_first_use(mixed, batch):
     x.zero_()
     pf.pf_linear_solve(g, dev(np.abs(s)), dev(b), x, pf.pf_lin_opts_default(rel_tol=1e-12))
     assert _rel(x.cpu().numpy(), ref) <= 1e-9
+
+
+@pytest.mark.parametrize("kind", ["none", "class", "node"])
+def test_on_chip_solve_is_the_same_whatever_was_timed_before(kind):
+    """The same on-chip solve before and after calls that time launch shapes on
+    its grid (residual, products, a solve by the two-kernel iteration): bit for
+    bit, iterations included."""
+    pf = _pf()
+    p, sig, b = _blocks(38, 43, 52 + len(kind), (D,) * 6)
+    s, b = dev(sig[kind]), dev(b)
+    g = pf.grid_from_problem(p)
+    opts = pf.pf_lin_opts_default(rel_tol=1e-12)
+    out = []
+    for k in range(4):
+        x = torch.zeros_like(b)
+        print(kind, k, flush=True)
+        info = pf.pf_linear_solve(g, s, b, x, opts)
+        out.append((x.cpu().numpy().tobytes(), info["iters"], info["rel_res"]))
+        r, y = torch.empty_like(b), torch.empty_like(b)
+        if k == 0:
+            rel = pf.pf_residual(g, s, b, x, r)
+            assert rel == pytest.approx(info["rel_res"], rel=1e-6)
+            rn = torch.empty_like(b)
+            assert pf.pf_residual_noalloc(g, s, b, x, rn) == rel and torch.equal(r, rn)
+        elif k == 1:
+            pf.pf_spmv(g, s, x, y, 0)
+            pf.pf_spmv(g, s, x, y, 1)
+        else:
+            _solve(pf, g, s, b, False, chip=False)
+    assert all(o == out[0] for o in out)
