@@ -170,7 +170,7 @@ __device__ __forceinline__ float uni(float x)
 // division's result would stay in a vector register).
 __device__ __forceinline__ int cut(int o, int n, int c, int t)
 {
-    return o + __builtin_amdgcn_readfirstlane(t * n / c);   // t n < 2^18
+    return o + __builtin_amdgcn_readfirstlane(t * n / c);   // t <= 256 tiles, n <= 512 nodes each: t n <= 2^25
 }
 
 constexpr unsigned CH_DIR = 0x80000000u;
@@ -1059,7 +1059,6 @@ hipError_t chip_launch(int form, int kz, const ChipSys<T> *table, const int *fir
     case CHF_NONE * 100 + 16: return launch_k<T, CHF_NONE, 16>(table, first, nsys, tiles, s);
     case CHF_NODE * 100 + 4: return launch_k<T, CHF_NODE, 4>(table, first, nsys, tiles, s);
     case CHF_NODE * 100 + 8: return launch_k<T, CHF_NODE, 8>(table, first, nsys, tiles, s);
-    case CHF_NODE * 100 + 16: return launch_k<T, CHF_NODE, 16>(table, first, nsys, tiles, s);
     case CHF_CLASS * 100 + 4: return launch_k<T, CHF_CLASS, 4>(table, first, nsys, tiles, s);
     case CHF_CLASS * 100 + 8: return launch_k<T, CHF_CLASS, 8>(table, first, nsys, tiles, s);
     case CHF_CLASS * 100 + 16: return launch_k<T, CHF_CLASS, 16>(table, first, nsys, tiles, s);
