@@ -437,6 +437,13 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
     }
     const T ceps = S.ceps, cdiag = S.cdiag, cidiag = S.cidiag;
 
+    // Cell a of staged plane k.  An address beyond the 16 bits of an LDS
+    // instruction's offset is computed here (outside of the iteration loop it
+    // would take a register, which the 16-plane instances reload from memory).
+    auto cell = [&](const int k, const int a) -> T & {
+        return L[((k + 1) * LP * (int)sizeof(T) > 0xffff ? here(a) : a) + k * LP];
+    };
+
     // A q (aq) and D^-1 A q (hat) at planes k0 .. k0 + PG - 1 of the own column,
     // with the diagonal D; q in registers, its z halo in zl, zh.  The LDS reads
     // of all planes go out first.  A wave whose nodes and neighbours are all of
@@ -446,11 +453,10 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
         T l[PG][4], zd[PG], zu[PG], sum[PG], iD[PG], qc[PG + 2];
 #pragma unroll
         for (int e = 0; e < PG; ++e) {
-                const T *const Lk = L + (k0 + e) * LP;
-            l[e][0] = Lk[axm];
-            l[e][1] = Lk[axp];
-            l[e][2] = Lk[aym];
-            l[e][3] = Lk[ayp];
+            l[e][0] = cell(k0 + e, axm);
+            l[e][1] = cell(k0 + e, axp);
+            l[e][2] = cell(k0 + e, aym);
+            l[e][3] = cell(k0 + e, ayp);
         }
 #pragma unroll
         for (int e = 0; e < PG + 2; ++e) {   // planes k0 - 1 .. k0 + PG
@@ -586,7 +592,7 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
         __syncthreads();   // the staged planes have been read
 #pragma unroll
         for (int k = 0; k < KZ; ++k)
-            if (k / UG * UG < nk) L[k * LP + aw] = val[k];
+            if (k / UG * UG < nk) cell(k, aw) = val[k];
         wave_sums<NQ>(acc);
         if ((tid & 63) == 63) {
 #pragma unroll
@@ -608,8 +614,8 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
             double s = bred[0][tid];
 #pragma unroll
             for (int w = 1; w < NW; ++w) s += bred[w][tid];
-            const unsigned at = (unsigned)(tid * grow + (lb - gat)) * 16u, sb = (n & 1) * SB1 + gbase;
-            if (near & 64u) xput<0>(xs, at, sb, s, tag0 + n);
+            const unsigned at = (unsigned)((BIG ? here(tid) : tid) * grow + (lb - gat)) * 16u, sb = (n & 1) * SB1 + gbase;
+            if (!BIG && (near & 64u)) xput<0>(xs, at, sb, s, tag0 + n);
             else xput<SC1>(xs, at, sb, s, tag0 + n);
         }
         if constexpr (TAGGED) {
@@ -803,7 +809,7 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
                             xr[k] = xr[k] + al * po[e] + om * s;
                             p[k] = pn;
                         }
-                        L[k * LP + aw] = pn;
+                        cell(k, aw) = pn;
                     }
                 }
             }
@@ -821,7 +827,7 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
             for (int k = 0; k < KZ; ++k) {
                 if constexpr (BIG) PX[k * NT + tid] = r[k];
                 else p[k] = r[k];
-                L[k * LP + aw] = r[k];
+                cell(k, aw) = r[k];
             }
         }
 #pragma unroll
@@ -868,7 +874,7 @@ __global__ __launch_bounds__(CH_NT) void k_chip(const ChipSys<T> *__restrict__ t
         for (int k = 0; k < KZ; ++k) {
             if (k / UG * UG < nk) {
                 r[k] = r[k] - al * v[k];
-                L[k * LP + aw] = r[k];
+                cell(k, aw) = r[k];
             }
         }
 #pragma unroll
