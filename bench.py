@@ -10,6 +10,8 @@ single-GPU workload of the benchmark set.  All inputs are resident in device
 memory before the timed region starts.
 
 The JSON line also carries:
+  timed_kernel  what the timed steps spend their time on: the on-chip Krylov
+                kernel, which is bound by latency and so has no roofline here
   roofline      the batched BiCGSTAB step-A stencil kernel (the previous
                 iteration's x, r update, the p update and v = A p^ in one
                 pass over every iterating member) of the two-kernel
@@ -906,6 +908,12 @@ def main():
             "bytes_rule": ("77 B per node of every member still iterating at that launch: s^, p^, v^, t^, x "
                            "(8 B each) read, 1-byte coefficient palette index (it also selects the shift from "
                            "the member's per-class table), 4-byte shadow; x, r^, p^, v^ written"),
+        },
+        "timed_kernel": {
+            "kernel": "k_chip<double>, shift per class, 16 planes a tile: every member's Krylov run in one launch",
+            "bound": ("latency of the two exchanges among a member's tiles in each iteration, not HBM "
+                      "(profiles/onchip_runs_trace.md: counters and cycles)"),
+            "node_iters_per_s": node_iters / sec_per_step,
         },
     }
     if args.forms:
