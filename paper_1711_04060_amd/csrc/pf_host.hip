@@ -754,6 +754,7 @@ pf_status run_chunk(pf_grid *g, const OpDesc &op, Work<T> &w, int m, bool may_ti
 // Launch shapes chosen per (grid shape, precision) for this process: step A
 // (also used by the residual and product kernels) and step B.
 std::map<std::tuple<int, int, int, int>, std::pair<ZCfg, ZCfg>> g_tuned;
+std::mutex g_tuned_mu;   // of this and the other maps of shapes (grids of several threads)
 
 bool tuning_enabled()
 {
@@ -790,11 +791,14 @@ pf_status tune(pf_grid *g)
     if (done || !tuning_enabled()) return PF_OK;
     done = true;
     const auto key = std::make_tuple(g->nx, g->ny, g->nz, (int)sizeof(T));
-    auto found = g_tuned.find(key);
-    if (found != g_tuned.end()) {
-        cfg_ref<T>(g) = found->second.first;
-        cfgb_ref<T>(g) = found->second.second;
-        return PF_OK;
+    {
+        std::lock_guard<std::mutex> lock(g_tuned_mu);
+        auto found = g_tuned.find(key);
+        if (found != g_tuned.end()) {
+            cfg_ref<T>(g) = found->second.first;
+            cfgb_ref<T>(g) = found->second.second;
+            return PF_OK;
+        }
     }
     Work<T> &w = [&]() -> Work<T> & {
         if constexpr (sizeof(T) == 8) return g->w64;
@@ -882,7 +886,10 @@ pf_status tune(pf_grid *g)
     if (st != PF_OK) return st;
     cfg_ref<T>(g) = bestA;
     cfgb_ref<T>(g) = bestB;
-    g_tuned[key] = {bestA, bestB};
+    {
+        std::lock_guard<std::mutex> lock(g_tuned_mu);
+        g_tuned[key] = {bestA, bestB};
+    }
     if (getenv("PF_LOG"))
         fprintf(stderr,
                 "[pf] tuned %dx%dx%d %s: step A threads %d strip %d z-planes %d depth %d (%.1f us); "
@@ -910,11 +917,14 @@ pf_status tune_alone(pf_grid *g, const OpDesc &op, ZCfg &cfg, bool &done, ShapeM
 {
     if (done || !tuning_enabled()) return PF_OK;
     const auto key = std::make_tuple(g->nx, g->ny, g->nz, (int)sizeof(T));
-    auto found = kept.find(key);
-    if (found != kept.end()) {
-        cfg = found->second;
-        done = true;
-        return PF_OK;
+    {
+        std::lock_guard<std::mutex> lock(g_tuned_mu);
+        auto found = kept.find(key);
+        if (found != kept.end()) {
+            cfg = found->second;
+            done = true;
+            return PF_OK;
+        }
     }
     Work<T> &w = [&]() -> Work<T> & {
         if constexpr (sizeof(T) == 8) return g->w64;
@@ -964,7 +974,10 @@ pf_status tune_alone(pf_grid *g, const OpDesc &op, ZCfg &cfg, bool &done, ShapeM
     (void)hipEventDestroy(e1);
     if (st != PF_OK) return st;
     cfg = best;
-    kept[key] = best;
+    {
+        std::lock_guard<std::mutex> lock(g_tuned_mu);
+        kept[key] = best;
+    }
     done = true;
     if (getenv("PF_LOG"))
         fprintf(stderr, "[pf] tuned %dx%dx%d %s %s: threads %d strip %d z-planes %d depth %d (%.1f us)\n",

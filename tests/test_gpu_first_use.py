@@ -1,6 +1,8 @@
 """The first call of a kind on a grid shape, which times launch shapes before it
 does its work: refused input stays refused, results are those of later calls.
 (Sizes that no other test uses: the shapes are kept per size.)"""
+import threading
+
 import numpy as np
 import pytest
 
@@ -74,3 +76,31 @@ def test_on_chip_solve_is_the_same_whatever_was_timed_before(kind):
         else:
             _solve(pf, g, s, b, False, chip=False)
     assert all(o == out[0] for o in out)
+
+
+def test_first_calls_of_several_threads():
+    """Each thread times the launch shapes of its own grid's size; the maps that
+    keep them are the process's."""
+    pf = _pf()
+    jobs = []
+    for i in range(6):
+        p, sig, b = _field_of_many_values(30 + i, 21, 23)
+        jobs.append((p, dev(sig["node"]), dev(b), oracle.linear_solve(p, sig["node"], b, tol=1e-13)[0]))
+    errs = [None] * len(jobs)
+
+    def work(i):
+        p, s, b, ref = jobs[i]
+        g = pf.grid_from_problem(p)
+        x, r = torch.zeros_like(b), torch.empty_like(b)
+        pf.pf_residual(g, s, b, x, r)
+        pf.pf_linear_solve(g, s, b, x, pf.pf_lin_opts_default(rel_tol=1e-12))
+        pf.pf_spmv(g, s, x, r, 1)
+        errs[i] = (_rel(x.cpu().numpy(), ref), pf.pf_residual(g, s, b, x, r))
+
+    print("threads", flush=True)
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(jobs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert all(e is not None and e[0] <= 1e-9 and e[1] <= 1e-12 for e in errs), errs
