@@ -1312,7 +1312,7 @@ bool chip_fits(const LinSolve &L)
     return chip_geom(g, L.op.psi, chip_kzmax(L), chip_cap(g)).KZ > 0;
 }
 
-pf_status ls_round_launch(LinSolve &L);
+pf_status ls_round_residual(LinSolve &L);
 
 // Start of the next Krylov run: nothing to do yet for an on-chip run.
 template <typename T>
@@ -1321,16 +1321,14 @@ pf_status ls_start(LinSolve &L, double tol2, bool zero_x)
     L.run_tol2 = tol2;
     L.chip = chip_fits<T>(L) && chip_open(L.g, true);
     if (!L.chip) {
-        // an on-chip run was expected (set-up): the start is computed again,
-        // in the shapes of the two-kernel iteration
+        // an on-chip run was expected (set-up): the shapes of the two-kernel
+        // iteration are timed now, and the start computed again
         pf_grid *g = L.g;
-        if (L.rcfg) {
-            L.rcfg = nullptr;
+        if (tuning_enabled() && (!g->tuned || (sizeof(T) == 4 && !g->tuned32))) {
             PFCHK(tune<double>(g));
             if (sizeof(T) == 4) PFCHK(tune<T>(g));
-            PFCHK(ls_round_launch(L));
+            PFCHK(ls_round_residual(L));
             PFCHK(sync(g));
-            L.rr = g->hsc->red[0];
         }
         return krylov_start<T>(g, work_of<T>(g), L.rr, tol2, L.iter, L.o->max_iter, zero_x);
     }
@@ -1408,6 +1406,8 @@ pf_status chip_system(LinSolve &L, const pfk::ChipGeom &ge, int kz, bool whole, 
 
 template <typename T>
 pf_status krylov_run(pf_grid *g, const OpDesc &op, Work<T> &w, int m_fixed, int *status, bool adaptive);
+
+pf_status ls_round_launch(LinSolve &L);
 
 // A run meant for the chip by the two-kernel iteration after all (its memory
 // could not be had, or tiles gave up waiting), from the true residual of what
